@@ -141,7 +141,7 @@ const char* kernel_name(int id) {
         "k_lookup_fwd",   "k_debug_indices", "k_quant_bf16",    "k_quant_fp8",
         "k_atlas_to_buckets", "k_bwd_fragment", "k_fill_u32",   "k_radix_hist",
         "k_scan",         "k_radix_scatter", "k_bucket_ranges", "k_segacc",
-        "k_segacc_hot",   "k_combine_hot",   "k_segacc_big",    "k_bake_directions",
+        "k_combine_hot",  "k_segacc_big",    "k_bake_directions",
         "k_bake_env",     "k_build_mip",     "k_lookup_lod",    "k_pack_bits",
         "k_lookup_light", "k_bake_shadow",   "k_vq_assign",     "k_vq_hist",
         "k_vq_scatter",   "k_vq_pieces",     "k_vq_combine",    "k_lod_bwd_fragment",

@@ -8,15 +8,16 @@
 //                       key = bucket << cell_bits | (y0 n + x0).
 //   2. radix sort       stable LSD sort of (key, record) by digits of up to
 //                       10 bits (9 for large inputs): per-tile digit
-//                       histograms, one exclusive scan over (digit, tile),
+//                       histograms, one exclusive scan over (digit, tile)
+//                       (small sorts: added up by the scatter's workgroups),
 //                       stable in-tile ranking with wave ballots.  Equal keys
 //                       keep record order, so the sorted sequence depends only
 //                       on the inputs.
 //   3. k_bucket_ranges  [start, end) of every bucket in the sorted records.
-//      k_payload        (buckets of at most 64 records on average) the
-//                       fractions and weighted upstream gradient of the
-//                       records of buckets with at most 64 records, written in
-//                       sorted order.
+//      k_payload        (buckets of at most 64 records on average, in its
+//                       place) the same, and the fractions and weighted
+//                       upstream gradient of the records of buckets with at
+//                       most 64 records, written in sorted order.
 //   4. k_segacc         eight buckets per wavefront (pass 1): the records of a
 //                       bucket with at most 64 are held in a register window
 //                       (read from the payload, or gathered from the
@@ -27,7 +28,7 @@
 //                       Untouched buckets get zeros.  Buckets with 65..PIECE
 //                       records go to k_segacc_big (rounds of 64 with a
 //                       carry), more to pass 2.
-//   5. k_segacc_hot /   pass 2: hot buckets are cut at fixed chunk boundaries of
+//   5. k_segacc_big /   pass 2: hot buckets are cut at fixed chunk boundaries of
 //      k_combine_hot    the sorted records; each chunk's part is reduced as in
 //                       pass 1 into a partial tile, and the partials are summed
 //                       in chunk order.
@@ -171,13 +172,33 @@ __device__ __forceinline__ void nt_store2(float* p, float a, float b) {
     __builtin_nontemporal_store(b, p + 1);
 }
 
+// The words that the later passes expect at zero (the disorder word, the
+// counters, the bucket ranges), cleared by the launch that makes the records:
+// one launch fewer, and the stores hide behind the fragments' loads.  The host
+// asks for it when a thread clears at most CLEAR_QUADS 16-byte groups (a
+// 4096-fragment batch over a million buckets would clear 8 MB from 16
+// workgroups); otherwise quads is 0 and a fill launch does it.
+constexpr int64_t CLEAR_QUADS = 8;
+
+struct ClearWords {
+    uint4* at;
+    int64_t quads;
+};
+
+__device__ __forceinline__ void clear_words(const ClearWords& z) {
+    const int64_t stride = (int64_t)gridDim.x * 256;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < z.quads; i += stride)
+        z.at[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 template <int FMT, int C, int MODE>
 __global__ __launch_bounds__(256) void k_bwd_fragment(
     TexView t, const float* __restrict__ uv, const float* __restrict__ tbn,
     const float* __restrict__ view, const float* __restrict__ grad_out,
     float* __restrict__ grad_view, float* __restrict__ grad_uv, uint32_t* __restrict__ keys,
-    float* __restrict__ wrec, FragMap m, int cell_bits, uint32_t sentinel) {
+    float* __restrict__ wrec, FragMap m, int cell_bits, uint32_t sentinel, ClearWords clear) {
     __shared__ FragStage stage;
+    clear_words(clear);
     const int64_t f = frag_of(m, blockIdx.x, gridDim.x, threadIdx.x);
     const int n = t.n;
     float go[4] = {0.f, 0.f, 0.f, 0.f};
@@ -294,7 +315,8 @@ __global__ __launch_bounds__(256) void k_lod_bwd_fragment(
     const float* __restrict__ grad_out, LevelStarts start,
     float* __restrict__ grad_view, float* __restrict__ grad_uv, uint32_t* __restrict__ keys,
     float* __restrict__ wrec, float* __restrict__ gl, FragMap m, int cell_bits,
-    uint32_t sentinel) {
+    uint32_t sentinel, ClearWords clear) {
+    clear_words(clear);
     const int64_t f = frag_of(m, blockIdx.x, gridDim.x, threadIdx.x);
     if (f < 0) return;
     const int n = ls.n;
@@ -423,78 +445,122 @@ __device__ __forceinline__ bool sort_skipped(const uint32_t* __restrict__ disord
     return disorder != nullptr && __builtin_amdgcn_readfirstlane(*disorder) == 0u;
 }
 
-// Whether any key is smaller than the one before it, in two launches.  The
-// first writes one flag per workgroup of 1024 keys (four per thread with one
-// 16-byte load -- the key buffer is padded to 256 bytes -- and the keys
-// around them), the second ORs the flags into *disorder (cleared before) with
-// one atomic per 4096 flags.  On unsorted keys nearly every wave finds a
-// descent, and atomics of every wave on one address would serialise.
+// One 16-byte group of keys starting at i0 with the keys around it (the key
+// buffer is padded to 256 bytes, so the load of a partial last group stays
+// inside it): k[0] the key before, k[1..4] the group, k[5] the key after.
+__device__ __forceinline__ void load_key_group(const uint32_t* __restrict__ keys, int64_t i0,
+                                               int64_t R, uint32_t k[6]) {
+    const uint4 q = *(const uint4*)(keys + i0);
+    k[0] = keys[i0 > 0 ? i0 - 1 : 0];
+    k[1] = q.x;
+    k[2] = q.y;
+    k[3] = q.z;
+    k[4] = q.w;
+    k[5] = keys[i0 + 4 < R ? i0 + 4 : R - 1];
+}
+
+__device__ __forceinline__ bool group_descends(const uint32_t k[6], int64_t i0, int64_t R) {
+    bool down = false;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const int64_t i = i0 + u;
+        if (i > 0 && i < R && k[u + 1] < k[u]) down = true;
+    }
+    return down;
+}
+
+// The [start, end) of the buckets that start or end in a group of sorted keys.
+__device__ __forceinline__ void group_ranges(const uint32_t k[6], int64_t i0, int64_t R,
+                                             int cell_bits, int64_t nb, int2* __restrict__ range) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const int64_t i = i0 + u;
+        if (i >= R) break;
+        const uint32_t bu = k[u + 1] >> cell_bits;
+        if (bu >= nb) continue;  // records of a sparse plan without a bucket (sorted last)
+        if (i == 0 || (k[u] >> cell_bits) != bu) range[bu].x = (int)i;
+        if (i == R - 1 || (k[u + 2] >> cell_bits) != bu) range[bu].y = (int)(i + 1);
+    }
+}
+
+// Whether any key is smaller than the one before it: a workgroup of 1024 keys
+// that finds a descent stores 1 into *disorder (cleared before).  Every such
+// workgroup stores the same value with a plain store, so nothing serialises: an
+// atomic of every wave on this one word took 0.18 ms on 66M unsorted keys, and
+// a flag per workgroup ORed by a second launch cost that launch on every call.
 //
-// With `range` the first launch also writes the [start, end) of every bucket
-// as k_bucket_ranges forms them, from each workgroup whose 1024 keys (and
-// the key before them) are in order: when all are, the sort and
-// k_bucket_ranges return at once and these are the ranges; when some are not,
-// k_bucket_ranges writes both ends of every bucket the sorted keys hold (the
+// With `range` the check also writes the [start, end) of every bucket as
+// k_bucket_ranges forms them, from each workgroup whose 1024 keys (and the
+// key before them) are in order: when all are, the sort and k_bucket_ranges
+// return at once and these are the ranges; when some are not, k_bucket_ranges
+// (or k_payload) writes both ends of every bucket the sorted keys hold (the
 // same buckets these keys hold) after the sort, and buckets without keys keep
 // the zeros filled in before.  Unsorted keys make nearly every record a
 // boundary, so workgroups with a descent write nothing.
 __global__ __launch_bounds__(256) void k_keys_in_order(const uint32_t* __restrict__ keys, int64_t R,
-                                                       uint32_t* __restrict__ flags, int cell_bits,
-                                                       int64_t nb, int2* __restrict__ range) {
-    __shared__ uint32_t wave_down[4];
+                                                       uint32_t* __restrict__ disorder,
+                                                       int cell_bits, int64_t nb,
+                                                       int2* __restrict__ range) {
     const int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    bool down = false;
     uint32_t k[6] = {0u, 0u, 0u, 0u, 0u, 0u};
+    bool down = false;
     if (i0 < R) {
-        const uint4 q = *(const uint4*)(keys + i0);
-        k[0] = keys[i0 > 0 ? i0 - 1 : 0];
-        k[1] = q.x;
-        k[2] = q.y;
-        k[3] = q.z;
-        k[4] = q.w;
-        k[5] = keys[i0 + 4 < R ? i0 + 4 : R - 1];
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const int64_t i = i0 + u;
-            if (i > 0 && i < R && k[u + 1] < k[u]) down = true;
-        }
+        load_key_group(keys, i0, R, k);
+        down = group_descends(k, i0, R);
     }
-    const uint64_t m = __ballot(down);
-    if ((threadIdx.x & 63) == 0) wave_down[threadIdx.x >> 6] = m != 0ull ? 1u : 0u;
-    __syncthreads();
-    const uint32_t any = wave_down[0] | wave_down[1] | wave_down[2] | wave_down[3];
-    if (threadIdx.x == 0) flags[blockIdx.x] = any;
-    if (range && any == 0u && i0 < R) {
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const int64_t i = i0 + u;
-            if (i >= R) break;
-            const uint32_t bu = k[u + 1] >> cell_bits;
-            if (bu >= nb) continue;  // records of a sparse plan without a bucket
-            if (i == 0 || (k[u] >> cell_bits) != bu) range[bu].x = (int)i;
-            if (i == R - 1 || (k[u + 2] >> cell_bits) != bu) range[bu].y = (int)(i + 1);
-        }
-    }
+    const bool any = __syncthreads_or((int)down) != 0;
+    if (any && threadIdx.x == 0) *disorder = 1u;
+    if (range && !any && i0 < R) group_ranges(k, i0, R, cell_bits, nb, range);
 }
 
-__global__ __launch_bounds__(256) void k_flags_any(const uint32_t* __restrict__ flags,
-                                                   int64_t nflags,
-                                                   uint32_t* __restrict__ disorder) {
-    const int64_t f0 = (int64_t)blockIdx.x * 4096 + threadIdx.x;
-    uint32_t any = 0u;
+// The order check of a small sort, on one radix tile of SORT_TILE keys per
+// workgroup, which also counts the first pass's digits of its tile (the key's
+// lowest D bits) into counts[tile][digit], so that pass needs no launch of
+// k_radix_hist.
+template <int D>
+__global__ __launch_bounds__(256) void k_keys_in_order_hist(const uint32_t* __restrict__ keys,
+                                                            int64_t R,
+                                                            uint32_t* __restrict__ disorder,
+                                                            int cell_bits, int64_t nb,
+                                                            int2* __restrict__ range,
+                                                            uint32_t* __restrict__ counts) {
+    constexpr int B = 1 << D;
+    constexpr int GROUPS = SORT_TILE / 1024;
+    __shared__ uint32_t cnt[B];
+    const int t = threadIdx.x;
+    for (int d = t; d < B; d += 256) cnt[d] = 0;
+    const int64_t base = (int64_t)blockIdx.x * SORT_TILE + t * 4;
+    uint32_t k[GROUPS][6];
+    bool down = false;
 #pragma unroll
-    for (int u = 0; u < 16; u++) {
-        const int64_t f = f0 + 256 * u;
-        if (f < nflags) any |= flags[f];
+    for (int g = 0; g < GROUPS; g++) {
+        const int64_t i0 = base + g * 1024;
+        if (i0 < R) {
+            load_key_group(keys, i0, R, k[g]);
+            down = down || group_descends(k[g], i0, R);
+        }
     }
-    if (__syncthreads_or((int)any) && threadIdx.x == 0) atomicOr(disorder, 1u);
+    const bool any = __syncthreads_or((int)down) != 0;  // cnt is zero past this
+    if (any && t == 0) *disorder = 1u;
+#pragma unroll
+    for (int g = 0; g < GROUPS; g++) {
+        const int64_t i0 = base + g * 1024;
+        if (i0 >= R) break;
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (i0 + u < R) atomicAdd(&cnt[k[g][u + 1] & (B - 1)], 1u);
+        if (range && !any) group_ranges(k[g], i0, R, cell_bits, nb, range);
+    }
+    __syncthreads();
+    for (int d = t; d < B; d += 256) counts[(int64_t)blockIdx.x * B + d] = cnt[d];
 }
 
 // Digit counts of one tile of SORT_TILE keys: hist[d * tiles + tile].  Tiles
 // are renumbered so that each XCD takes a contiguous range: the counts of
 // neighbouring tiles share cache lines of the digit-major table, and so the
-// strided 4-byte stores of one XCD's tiles combine in its L2.
-template <int D>
+// strided 4-byte stores of one XCD's tiles combine in its L2.  SMALL (a small
+// sort, whose scatter adds the counts up itself): tile-major, hist[tile * B + d].
+template <int D, bool SMALL>
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(const uint32_t* __restrict__ keys,
                                                              int64_t R, int shift,
                                                              uint32_t* __restrict__ hist,
@@ -520,7 +586,8 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(const uint32_t* __r
         if (i < R) atomicAdd(&cnt[(k[r] >> shift) & (B - 1)], 1u);
     }
     __syncthreads();
-    for (int d = t; d < B; d += SORT_THREADS) hist[(int64_t)d * tiles + tile] = cnt[d];
+    for (int d = t; d < B; d += SORT_THREADS)
+        hist[SMALL ? tile * B + d : (int64_t)d * tiles + tile] = cnt[d];
 }
 
 // x from the lane `o` below in the wavefront, for a power of two o < 64;
@@ -690,7 +757,12 @@ __global__ __launch_bounds__(256) void k_scan_down(const uint32_t* __restrict__ 
 // memory.  Tiles are renumbered per XCD as in the histogram: a digit's runs
 // from neighbouring tiles are adjacent in the output, so their partial-line
 // stores meet in one L2.
-template <int D>
+//
+// SMALL: hoff holds the tiles' digit counts (tile-major) instead of their
+// scanned offsets, and the workgroup adds them up itself: every thread reads
+// its digits' column of the table, one row of B counts per tile.  That takes
+// the place of the two launches of the scan.
+template <int D, bool SMALL>
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int64_t R, int shift,
@@ -709,7 +781,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     const int64_t base = tile * SORT_TILE;
     for (int d = t; d < B; d += SORT_THREADS) {
         wcnt[0][d] = wcnt[1][d] = wcnt[2][d] = wcnt[3][d] = 0;
-        goff[d] = hoff[(int64_t)d * tiles + tile];
+        if constexpr (!SMALL) goff[d] = hoff[(int64_t)d * tiles + tile];
     }
     uint32_t k[SORT_IPT], v[SORT_IPT], loc[SORT_IPT];
     const int64_t wbase = base + w * QUARTER;
@@ -721,6 +793,30 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
         if (i < R) {
             k[r] = keys_in[i];
             v[r] = vals_in ? vals_in[i] : (uint32_t)i;
+        }
+    }
+    if constexpr (SMALL) {
+        // thread t's digits t DPT ..: their counts in the tiles before this
+        // one, and in all
+        uint32_t before[DPT], all[DPT], mine = 0;
+#pragma unroll
+        for (int j = 0; j < DPT; j++) before[j] = all[j] = 0;
+#pragma unroll 8
+        for (int q = 0; q < (int)tiles; q++) {
+#pragma unroll
+            for (int j = 0; j < DPT; j++) {
+                const uint32_t c = hoff[q * B + t * DPT + j];
+                all[j] += c;
+                before[j] += q < (int)tile ? c : 0u;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < DPT; j++) mine += all[j];
+        uint32_t start = block_exclusive(mine, wsum, nullptr);
+#pragma unroll
+        for (int j = 0; j < DPT; j++) {
+            goff[t * DPT + j] = start + before[j];
+            start += all[j];
         }
     }
     __syncthreads();
@@ -800,9 +896,7 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, int6
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-// Four sorted keys per thread (one 16-byte load; the key buffer is padded to
-// 256 bytes, so the load of a partial last group stays inside it) and the
-// two neighbours, loaded unconditionally from clamped positions.
+// Four sorted keys per thread, as in the order check.
 __global__ __launch_bounds__(256) void k_bucket_ranges(const uint32_t* __restrict__ skeys,
                                                        int64_t R, int cell_bits, int64_t nb,
                                                        int2* __restrict__ range,
@@ -811,38 +905,35 @@ __global__ __launch_bounds__(256) void k_bucket_ranges(const uint32_t* __restric
     if (sort_skipped(disorder)) return;
     const int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i0 >= R) return;
-    const uint4 q = *(const uint4*)(skeys + i0);
-    const uint32_t prev = skeys[i0 > 0 ? i0 - 1 : 0];
-    const uint32_t next = skeys[i0 + 4 < R ? i0 + 4 : R - 1];
-    const uint32_t b[6] = {prev >> cell_bits, q.x >> cell_bits, q.y >> cell_bits,
-                           q.z >> cell_bits, q.w >> cell_bits, next >> cell_bits};
-#pragma unroll
-    for (int u = 0; u < 4; u++) {
-        const int64_t i = i0 + u;
-        if (i >= R) break;
-        const uint32_t bu = b[u + 1];
-        if (bu >= nb) continue;  // records of a sparse plan without a bucket (sorted last)
-        if (i == 0 || b[u] != bu) range[bu].x = (int)i;
-        if (i == R - 1 || b[u + 2] != bu) range[bu].y = (int)(i + 1);
-    }
+    uint32_t k[6];
+    load_key_group(skeys, i0, R, k);
+    group_ranges(k, i0, R, cell_bits, nb, range);
 }
 
-// One sorted record's payload (records of buckets with more than 64 records
-// are skipped: their passes gather).
+// One sorted record: the ends of its bucket's range where it is the bucket's
+// first or last, and its payload unless its bucket holds more than 64 records
+// (their passes gather).  A record tells that from the keys 64 positions
+// before and after it; the middle of a bucket of 65 to 127 records cannot, and
+// writes a payload that nothing reads.
 template <int C, int MODE>
 __device__ __forceinline__ void payload_record(const uint32_t* __restrict__ skeys,
                                                const uint32_t* __restrict__ svals,
                                                const float* __restrict__ wrec,
                                                const float* __restrict__ grad_out,
-                                               const int2* __restrict__ range, int64_t i,
+                                               int2* __restrict__ range, int64_t i, int64_t R,
                                                int cell_bits, int64_t nb,
                                                float* __restrict__ payf,
                                                float* __restrict__ payg) {
     const uint32_t b = skeys[i] >> cell_bits;
     if (b >= nb) return;
-    const int2 r = range[b];
-    if (r.y - r.x > 64) return;
     const uint32_t rec = svals[i];
+    const uint32_t lo = skeys[i >= 1 ? i - 1 : 0] >> cell_bits;
+    const uint32_t hi = skeys[i + 1 < R ? i + 1 : R - 1] >> cell_bits;
+    const uint32_t lo64 = skeys[i >= 64 ? i - 64 : 0] >> cell_bits;
+    const uint32_t hi64 = skeys[i + 64 < R ? i + 64 : R - 1] >> cell_bits;
+    if (i == 0 || lo != b) range[b].x = (int)i;
+    if (i == R - 1 || hi != b) range[b].y = (int)(i + 1);
+    if ((i >= 64 && lo64 == b) || (i + 64 < R && hi64 == b)) return;
     float fx, fy, wb = 1.f;
     int64_t frag;
     if constexpr (MODE == MODE_NEAREST) {
@@ -873,28 +964,30 @@ __device__ __forceinline__ void payload_record(const uint32_t* __restrict__ skey
     }
 }
 
-// The payload of the sorted records of buckets with at most 64 records (the
-// ones the first accumulation pass serves from its register window), in
-// sorted order: the fractions (fx, fy) and the upstream gradient times the
-// bucket weight (1 in nearest mode).  That pass then reads its records
-// contiguously instead of gathering them from the fragments; the passes for
-// bigger buckets, whose records share cache lines, keep gathering.  Records
-// past the last bucket (sparse plans) are skipped.  Workgroups are renumbered
-// per XCD (neighbouring records gather from neighbouring fragments); a
-// workgroup takes PAYLOAD_PER_THREAD x 256 consecutive records, a thread every
-// 256th of them with its loads issued together, which also keeps the launch
-// small when the records came in key order and there is nothing to do.
+// The bucket ranges of the sorted records and the payload of the records of
+// buckets with at most 64 (the ones the first accumulation pass serves from
+// its register window), in sorted order: the fractions (fx, fy) and the
+// upstream gradient times the bucket weight (1 in nearest mode).  That pass
+// then reads its records contiguously instead of gathering them from the
+// fragments; the passes for bigger buckets, whose records share cache lines,
+// keep gathering.  Records past the last bucket (sparse plans) are skipped.
+// Workgroups are renumbered per XCD (neighbouring records gather from
+// neighbouring fragments); a workgroup takes PAYLOAD_PER_THREAD x 256
+// consecutive records, a thread every 256th of them with its loads issued
+// together, which also keeps the launch small when the records came in key
+// order and there is nothing to do.
 template <int C, int MODE>
 __global__ __launch_bounds__(256) void k_payload(const uint32_t* __restrict__ skeys,
                                                  const uint32_t* __restrict__ svals,
                                                  const float* __restrict__ wrec,
                                                  const float* __restrict__ grad_out,
-                                                 const int2* __restrict__ range, int64_t R,
+                                                 int2* __restrict__ range, int64_t R,
                                                  int cell_bits, int64_t nb,
                                                  float* __restrict__ payf,
                                                  float* __restrict__ payg,
                                                  const uint32_t* __restrict__ disorder) {
-    // records in key order are read where they were made: no payload
+    // records in key order are read where they were made: no payload, and the
+    // order check wrote their ranges
     if (sort_skipped(disorder)) return;
     const int64_t base =
         (int64_t)xcd_block_id(blockIdx.x, gridDim.x) * (256 * PAYLOAD_PER_THREAD) + threadIdx.x;
@@ -902,7 +995,7 @@ __global__ __launch_bounds__(256) void k_payload(const uint32_t* __restrict__ sk
     for (int k = 0; k < PAYLOAD_PER_THREAD; k++) {
         const int64_t i = base + 256 * k;
         if (i < R)
-            payload_record<C, MODE>(skeys, svals, wrec, grad_out, range, i, cell_bits, nb, payf,
+            payload_record<C, MODE>(skeys, svals, wrec, grad_out, range, i, R, cell_bits, nb, payf,
                                     payg);
     }
 }
@@ -1340,86 +1433,76 @@ __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ ske
     }
 }
 
-// Buckets with 65..PIECE records, listed by k_segacc: workgroup x serves list
-// x mod BIG_LISTS, one wavefront per listed bucket, rounds of 64 records with a
-// carry.
+// Buckets with 65..PIECE records, listed by k_segacc (the first big_blocks
+// workgroups): workgroup x serves list x mod BIG_LISTS, one wavefront per
+// listed bucket, rounds of 64 records with a carry.
+//
+// The workgroups after them are pass 2a, one wavefront per fixed chunk of PIECE
+// sorted records: a hot bucket overlapping the chunk (only the chunk's first
+// or last bucket can be hot) gets a partial tile, slot 0 for the first bucket
+// and slot 1 for the last.  They return at once when k_segacc saw no such
+// bucket.
 template <int C, int MODE>
 __global__ __launch_bounds__(256) void k_segacc_big(const uint32_t* __restrict__ skeys,
                                                     const uint32_t* __restrict__ svals,
                                                     const float* __restrict__ wrec,
                                                     const float* __restrict__ grad_out,
                                                     const int2* __restrict__ range,
-                                                    const TileOut out, int n,
-                                                    uint32_t cell_mask,
+                                                    const TileOut out, int n, int cell_bits,
                                                     const uint32_t* __restrict__ big_count,
                                                     const uint32_t* __restrict__ big_list,
-                                                    int64_t big_cap,
+                                                    int64_t big_cap, uint32_t big_blocks,
+                                                    float* __restrict__ part, int64_t R,
+                                                    int64_t nb,
                                                     const uint32_t* __restrict__ keys_made,
                                                     const uint32_t* __restrict__ disorder) {
+    const bool hot = blockIdx.x >= big_blocks;
+    if (hot && __builtin_amdgcn_readfirstlane(big_count[HOT_FLAG]) == 0u) return;
     if (sort_skipped(disorder)) {
         skeys = keys_made;
         svals = nullptr;
     }
     extern __shared__ float lds[];
     const int te = n * n * C;
+    const uint32_t cell_mask = cell_bits >= 32 ? 0xFFFFFFFFu : ((1u << cell_bits) - 1u);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float* tile = lds + w * te;
-    const uint32_t list = blockIdx.x % BIG_LISTS;
-    const uint32_t part = blockIdx.x / BIG_LISTS, parts = gridDim.x / BIG_LISTS;
-    const uint32_t count = __builtin_amdgcn_readfirstlane(big_count[list * BIG_STRIDE]);
-    const uint32_t* entries = big_list + list * big_cap;
-    const uint32_t stride = parts * 4;
-    // the next listed bucket and its range are read while this one is summed
-    uint32_t e = part * 4 + w;
-    uint32_t b_next = 0;
-    int2 r_next = make_int2(0, 0);
-    if (e < count) {
-        b_next = __builtin_amdgcn_readfirstlane(entries[e]);
-        r_next = range[b_next];
-    }
-    for (; e < count; e += stride) {
-        const uint32_t b = b_next;
-        const int rx = __builtin_amdgcn_readfirstlane(r_next.x);
-        const int ry = __builtin_amdgcn_readfirstlane(r_next.y);
-        if (e + stride < count) {
-            b_next = __builtin_amdgcn_readfirstlane(entries[e + stride]);
+    if (!hot) {
+        const uint32_t list = blockIdx.x % BIG_LISTS;
+        const uint32_t lpart = blockIdx.x / BIG_LISTS, parts = big_blocks / BIG_LISTS;
+        const uint32_t count = __builtin_amdgcn_readfirstlane(big_count[list * BIG_STRIDE]);
+        const uint32_t* entries = big_list + list * big_cap;
+        const uint32_t stride = parts * 4;
+        // the next listed bucket and its range are read while this one is summed
+        uint32_t e = lpart * 4 + w;
+        uint32_t b_next = 0;
+        int2 r_next = make_int2(0, 0);
+        if (e < count) {
+            b_next = __builtin_amdgcn_readfirstlane(entries[e]);
             r_next = range[b_next];
         }
-        float* dst = tile_dst(out, b, te);
-        if (!dst) continue;
-        tile_zero(tile, te);
-        reduce_records<C, MODE>(skeys, svals, wrec, grad_out, rx, ry, n, cell_mask, tile);
-        tile_store(tile, dst, te);
+        for (; e < count; e += stride) {
+            const uint32_t b = b_next;
+            const int rx = __builtin_amdgcn_readfirstlane(r_next.x);
+            const int ry = __builtin_amdgcn_readfirstlane(r_next.y);
+            if (e + stride < count) {
+                b_next = __builtin_amdgcn_readfirstlane(entries[e + stride]);
+                r_next = range[b_next];
+            }
+            float* dst = tile_dst(out, b, te);
+            if (!dst) continue;
+            tile_zero(tile, te);
+            reduce_records<C, MODE>(skeys, svals, wrec, grad_out, rx, ry, n, cell_mask, tile);
+            tile_store(tile, dst, te);
+        }
+        return;
     }
-}
-
-// pass 2a: one wavefront per fixed chunk of PIECE sorted records; a hot bucket
-// overlapping the chunk (only the chunk's first or last bucket can be hot)
-// gets a partial tile, slot 0 for the first bucket and slot 1 for the last.
-template <int C, int MODE>
-__global__ __launch_bounds__(64) void k_segacc_hot(const uint32_t* __restrict__ skeys,
-                                                   const uint32_t* __restrict__ svals,
-                                                   const float* __restrict__ wrec,
-                                                   const float* __restrict__ grad_out,
-                                                   const int2* __restrict__ range,
-                                                   float* __restrict__ part, int64_t R, int n,
-                                                   int cell_bits, int64_t nb,
-                                                   const uint32_t* __restrict__ keys_made,
-                                                   const uint32_t* __restrict__ disorder,
-                                                   const uint32_t* __restrict__ hot) {
-    if (__builtin_amdgcn_readfirstlane(hot[0]) == 0u) return;  // no bucket for pass 2
-    if (sort_skipped(disorder)) {
-        skeys = keys_made;
-        svals = nullptr;
-    }
-    extern __shared__ float lds[];
-    const int te = n * n * C;
-    const uint32_t cell_mask = (cell_bits >= 32) ? 0xFFFFFFFFu : ((1u << cell_bits) - 1u);
-    const int64_t k = blockIdx.x;
+    const int64_t k = (int64_t)(blockIdx.x - big_blocks) * 4 + w;
     const int64_t c0 = k * PIECE;
+    if (c0 >= R) return;
     const int64_t c1 = (c0 + PIECE < R) ? c0 + PIECE : R;
-    const uint32_t bf = skeys[c0] >> cell_bits;
-    const uint32_t bl = skeys[c1 - 1] >> cell_bits;
+    const uint32_t bf = __builtin_amdgcn_readfirstlane(skeys[c0]) >> cell_bits;
+    const uint32_t bl = __builtin_amdgcn_readfirstlane(skeys[c1 - 1]) >> cell_bits;
     for (int slot = 0; slot < 2; slot++) {
         const uint32_t b = slot == 0 ? bf : bl;
         if (slot == 1 && bl == bf) break;
@@ -1428,10 +1511,9 @@ __global__ __launch_bounds__(64) void k_segacc_hot(const uint32_t* __restrict__ 
         if ((int64_t)r.y - r.x <= PIECE) continue;
         const int64_t a = r.x > c0 ? r.x : c0;
         const int64_t e = r.y < c1 ? r.y : c1;
-        tile_zero(lds, te);
-        reduce_records<C, MODE>(skeys, svals, wrec, grad_out, a, e, n, cell_mask, lds);
-        tile_store(lds, part + (k * 2 + slot) * (int64_t)te, te);
-        wave_lds_sync();
+        tile_zero(tile, te);
+        reduce_records<C, MODE>(skeys, svals, wrec, grad_out, a, e, n, cell_mask, tile);
+        tile_store(tile, part + (k * 2 + slot) * (int64_t)te, te);
     }
 }
 
@@ -1548,9 +1630,12 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
     p->off_hist = take((size_t)p->scan_len * 4);
     p->off_hoff = take((size_t)p->scan_len * 4);
     p->off_scanp = take((size_t)(p->scan_blocks + 1) * 4);
-    // the disorder word, then one order flag per 1024 records
-    p->off_disorder = take((size_t)(ORDER_FLAGS_AT + (R + 1023) / 1024) * 4);
+    // the disorder word, and right after it (both are cleared in one go) the
+    // big-bucket counters and the bucket ranges
+    p->off_disorder = take(256);
     p->sort_total = o;
+    p->off_range = take((size_t)BIG_LISTS * BIG_STRIDE * 4 + (size_t)nb * 8);
+    p->clear_bytes = o - p->off_disorder;
     p->off_wrec = take((size_t)N * (mode == MODE_NEAREST ? 8 : 16));
     p->off_payf = take((size_t)R * 8);
     p->off_payg = take((size_t)R * 4 * C);
@@ -1562,7 +1647,6 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
     const int64_t runs_per_list = (ngroups + BIG_RUN * BIG_LISTS - 1) / (BIG_RUN * BIG_LISTS);
     const int64_t per_list = runs_per_list * BIG_RUN * SEG_GROUP;
     p->big_cap = std::max<int64_t>(1, std::min<int64_t>(per_list, R / 65));
-    p->off_range = take((size_t)BIG_LISTS * BIG_STRIDE * 4 + (size_t)nb * 8);
     p->off_biglist = take((size_t)BIG_LISTS * p->big_cap * 4);
     p->off_part = take((size_t)p->chunks * 2 * p->tile_elems * 4);
     p->total = o;
@@ -1573,13 +1657,13 @@ template <int FMT, int MODE>
 static void launch_bwd_fragment_c(const TexView& t, const float* uv, const float* tbn,
                                   const float* view, const float* go, float* gview, float* guv,
                                   uint32_t* keys, float* wrec, const FragMap& m, int cell_bits,
-                                  uint32_t sentinel, hipStream_t s) {
+                                  uint32_t sentinel, const ClearWords& clear, hipStream_t s) {
     const uint32_t blocks = fragmap_blocks(m);
     switch (t.C) {
-    case 1: hipLaunchKernelGGL((k_bwd_fragment<FMT, 1, MODE>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, view, go, gview, guv, keys, wrec, m, cell_bits, sentinel); break;
-    case 2: hipLaunchKernelGGL((k_bwd_fragment<FMT, 2, MODE>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, view, go, gview, guv, keys, wrec, m, cell_bits, sentinel); break;
-    case 3: hipLaunchKernelGGL((k_bwd_fragment<FMT, 3, MODE>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, view, go, gview, guv, keys, wrec, m, cell_bits, sentinel); break;
-    default: hipLaunchKernelGGL((k_bwd_fragment<FMT, 4, MODE>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, view, go, gview, guv, keys, wrec, m, cell_bits, sentinel); break;
+    case 1: hipLaunchKernelGGL((k_bwd_fragment<FMT, 1, MODE>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, view, go, gview, guv, keys, wrec, m, cell_bits, sentinel, clear); break;
+    case 2: hipLaunchKernelGGL((k_bwd_fragment<FMT, 2, MODE>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, view, go, gview, guv, keys, wrec, m, cell_bits, sentinel, clear); break;
+    case 3: hipLaunchKernelGGL((k_bwd_fragment<FMT, 3, MODE>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, view, go, gview, guv, keys, wrec, m, cell_bits, sentinel, clear); break;
+    default: hipLaunchKernelGGL((k_bwd_fragment<FMT, 4, MODE>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, view, go, gview, guv, keys, wrec, m, cell_bits, sentinel, clear); break;
     }
 }
 
@@ -1601,35 +1685,22 @@ static void launch_segacc_c(int C, dim3 grid, size_t shm, hipStream_t s, const u
 template <int MODE>
 static void launch_segacc_big_c(int C, dim3 grid, size_t shm, hipStream_t s, const uint32_t* sk,
                                 const uint32_t* sv, const float* wrec, const float* go,
-                                const int2* range, const TileOut& gt, int n, uint32_t mask,
+                                const int2* range, const TileOut& gt, int n, int cb,
                                 const uint32_t* bc, const uint32_t* bl, int64_t cap,
+                                uint32_t big_blocks, float* part, int64_t R, int64_t nb,
                                 const uint32_t* km, const uint32_t* dis) {
     switch (C) {
-    case 1: hipLaunchKernelGGL((k_segacc_big<1, MODE>), grid, dim3(256), shm, s, sk, sv, wrec, go, range, gt, n, mask, bc, bl, cap, km, dis); break;
-    case 2: hipLaunchKernelGGL((k_segacc_big<2, MODE>), grid, dim3(256), shm, s, sk, sv, wrec, go, range, gt, n, mask, bc, bl, cap, km, dis); break;
-    case 3: hipLaunchKernelGGL((k_segacc_big<3, MODE>), grid, dim3(256), shm, s, sk, sv, wrec, go, range, gt, n, mask, bc, bl, cap, km, dis); break;
-    default: hipLaunchKernelGGL((k_segacc_big<4, MODE>), grid, dim3(256), shm, s, sk, sv, wrec, go, range, gt, n, mask, bc, bl, cap, km, dis); break;
-    }
-}
-
-template <int MODE>
-static void launch_segacc_hot_c(int C, dim3 grid, size_t shm, hipStream_t s, const uint32_t* sk,
-                                const uint32_t* sv, const float* wrec, const float* go,
-                                const int2* range, float* part, int64_t R, int n, int cb,
-                                int64_t nb, const uint32_t* km, const uint32_t* dis,
-                                const uint32_t* hot) {
-    switch (C) {
-    case 1: hipLaunchKernelGGL((k_segacc_hot<1, MODE>), grid, dim3(64), shm, s, sk, sv, wrec, go, range, part, R, n, cb, nb, km, dis, hot); break;
-    case 2: hipLaunchKernelGGL((k_segacc_hot<2, MODE>), grid, dim3(64), shm, s, sk, sv, wrec, go, range, part, R, n, cb, nb, km, dis, hot); break;
-    case 3: hipLaunchKernelGGL((k_segacc_hot<3, MODE>), grid, dim3(64), shm, s, sk, sv, wrec, go, range, part, R, n, cb, nb, km, dis, hot); break;
-    default: hipLaunchKernelGGL((k_segacc_hot<4, MODE>), grid, dim3(64), shm, s, sk, sv, wrec, go, range, part, R, n, cb, nb, km, dis, hot); break;
+    case 1: hipLaunchKernelGGL((k_segacc_big<1, MODE>), grid, dim3(256), shm, s, sk, sv, wrec, go, range, gt, n, cb, bc, bl, cap, big_blocks, part, R, nb, km, dis); break;
+    case 2: hipLaunchKernelGGL((k_segacc_big<2, MODE>), grid, dim3(256), shm, s, sk, sv, wrec, go, range, gt, n, cb, bc, bl, cap, big_blocks, part, R, nb, km, dis); break;
+    case 3: hipLaunchKernelGGL((k_segacc_big<3, MODE>), grid, dim3(256), shm, s, sk, sv, wrec, go, range, gt, n, cb, bc, bl, cap, big_blocks, part, R, nb, km, dis); break;
+    default: hipLaunchKernelGGL((k_segacc_big<4, MODE>), grid, dim3(256), shm, s, sk, sv, wrec, go, range, gt, n, cb, bc, bl, cap, big_blocks, part, R, nb, km, dis); break;
     }
 }
 
 template <int MODE>
 static void launch_payload_c(int C, dim3 grid, hipStream_t s, const uint32_t* sk,
                              const uint32_t* sv, const float* wrec, const float* go,
-                             const int2* range, int64_t R, int cb, int64_t nb, float* pf,
+                             int2* range, int64_t R, int cb, int64_t nb, float* pf,
                              float* pg, const uint32_t* dis) {
     switch (C) {
     case 1: hipLaunchKernelGGL((k_payload<1, MODE>), grid, dim3(256), 0, s, sk, sv, wrec, go, range, R, cb, nb, pf, pg, dis); break;
@@ -1669,6 +1740,14 @@ hipError_t launch_exclusive_scan(const uint32_t* in, uint32_t* out, uint32_t* pa
     return hipGetLastError();
 }
 
+// What the per-fragment launch of `blocks` workgroups clears: everything, or
+// nothing when that is too much for its threads (see CLEAR_QUADS).
+static ClearWords clear_in_launch(const BwdPlan& plan, void* ws, uint32_t blocks) {
+    const int64_t quads = (int64_t)(plan.clear_bytes / 16);
+    if (quads > CLEAR_QUADS * 256 * (int64_t)blocks) return ClearWords{nullptr, 0};
+    return ClearWords{(uint4*)((char*)ws + plan.off_disorder), quads};
+}
+
 hipError_t launch_backward(const TexView& t, int fmt, int mode, const float* uv,
                            const float* tbn, const float* view, const float* grad_out,
                            float* grad_tex, float* grad_view, float* grad_uv,
@@ -1679,19 +1758,21 @@ hipError_t launch_backward(const TexView& t, int fmt, int mode, const float* uv,
     uint32_t* keys0 = (uint32_t*)(wsb + plan.off_keys0);
     float* wrec = (float*)(wsb + plan.off_wrec);
     const bool want_tex = grad_tex != nullptr;
+    ClearWords clear{nullptr, 0};
+    if (want_tex && N > 0) clear = clear_in_launch(plan, ws, fragmap_blocks(m));
 
     // 1. per fragment
     if (N > 0 && (want_tex || grad_view || grad_uv)) {
         prof_begin(K_BWD_FRAGMENT, s);
         uint32_t* kp = want_tex ? keys0 : nullptr;
         if (mode == MODE_NEAREST) {
-            if (fmt == FMT_F32) launch_bwd_fragment_c<FMT_F32, MODE_NEAREST>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, s);
-            else if (fmt == FMT_BF16) launch_bwd_fragment_c<FMT_BF16, MODE_NEAREST>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, s);
-            else launch_bwd_fragment_c<FMT_FP8, MODE_NEAREST>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, s);
+            if (fmt == FMT_F32) launch_bwd_fragment_c<FMT_F32, MODE_NEAREST>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, clear, s);
+            else if (fmt == FMT_BF16) launch_bwd_fragment_c<FMT_BF16, MODE_NEAREST>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, clear, s);
+            else launch_bwd_fragment_c<FMT_FP8, MODE_NEAREST>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, clear, s);
         } else {
-            if (fmt == FMT_F32) launch_bwd_fragment_c<FMT_F32, MODE_BILINEAR>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, s);
-            else if (fmt == FMT_BF16) launch_bwd_fragment_c<FMT_BF16, MODE_BILINEAR>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, s);
-            else launch_bwd_fragment_c<FMT_FP8, MODE_BILINEAR>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, s);
+            if (fmt == FMT_F32) launch_bwd_fragment_c<FMT_F32, MODE_BILINEAR>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, clear, s);
+            else if (fmt == FMT_BF16) launch_bwd_fragment_c<FMT_BF16, MODE_BILINEAR>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, clear, s);
+            else launch_bwd_fragment_c<FMT_FP8, MODE_BILINEAR>(t, uv, tbn, view, grad_out, grad_view, grad_uv, kp, wrec, m, plan.cell_bits, plan.sentinel, clear, s);
         }
         prof_end(K_BWD_FRAGMENT, s);
         hipError_t e = hipGetLastError();
@@ -1704,15 +1785,24 @@ hipError_t launch_backward(const TexView& t, int fmt, int mode, const float* uv,
     out.start[0] = 0;
     out.start[1] = (int64_t)t.W * t.H;
     out.grad[0] = grad_tex;
-    return launch_accumulate(t.n, t.C, mode, grad_out, out, plan, ws, s);
+    return launch_accumulate(t.n, t.C, mode, grad_out, out, plan, ws, clear.quads > 0, s);
 }
 
-// The stable sort of the R records' keys in keys0 (record numbers implied by
-// position).  The sorted keys and their record numbers end in *skeys, *svals.
-// disorder: NULL, or the device word k_keys_in_order wrote: when it holds 0
-// every launch returns at once (the keys are already in order).
-void launch_sort_records(const BwdPlan& plan, void* ws, const uint32_t* disorder, hipStream_t s,
-                         const uint32_t** skeys_out, const uint32_t** svals_out) {
+// Whether the R keys in keys0 are in order, and their stable sort (record
+// numbers implied by position) if they are not: the order check leaves 0 or 1
+// in the workspace's disorder word (cleared before, returned), and with 0
+// every launch of the sort returns at once.  With `range` (zero-filled before)
+// the check also writes the bucket ranges the keys give if they are in order.
+// The sorted keys and their record numbers end in *skeys, *svals.
+//
+// A sort of up to SMALL_SORT_TILES tiles is bound by its launches, so it makes
+// fewer: its order check counts the first pass's digits, and its scatters add
+// the counts up themselves (2 launches a pass, 1 for the first, instead of 4).
+// That costs every workgroup a read of the whole table of counts, which grows
+// as the square of the tiles over the launch.
+static const uint32_t* launch_sort_records(const BwdPlan& plan, void* ws, int2* range,
+                                           hipStream_t s, const uint32_t** skeys_out,
+                                           const uint32_t** svals_out) {
     char* wsb = (char*)ws;
     uint32_t* keys0 = (uint32_t*)(wsb + plan.off_keys0);
     uint32_t* keys1 = (uint32_t*)(wsb + plan.off_keys1);
@@ -1721,58 +1811,65 @@ void launch_sort_records(const BwdPlan& plan, void* ws, const uint32_t* disorder
     uint32_t* hist = (uint32_t*)(wsb + plan.off_hist);
     uint32_t* hoff = (uint32_t*)(wsb + plan.off_hoff);
     uint32_t* scanp = (uint32_t*)(wsb + plan.off_scanp);
+    uint32_t* disorder = (uint32_t*)(wsb + plan.off_disorder);
     const int64_t R = plan.records;
+    const bool small = plan.tiles <= SMALL_SORT_TILES;
+    const dim3 grid((uint32_t)plan.tiles), block(SORT_THREADS);
     const uint32_t* kin = keys0;
     const uint32_t* vin = nullptr;
+    prof_begin(K_ORDER_CHECK, s);
+    if (small) {
+        const int D = std::max(8, plan.digit_bits[0]);
+        if (D == 8) hipLaunchKernelGGL(k_keys_in_order_hist<8>, grid, block, 0, s, keys0, R, disorder, plan.cell_bits, plan.buckets, range, hist);
+        else if (D == 9) hipLaunchKernelGGL(k_keys_in_order_hist<9>, grid, block, 0, s, keys0, R, disorder, plan.cell_bits, plan.buckets, range, hist);
+        else hipLaunchKernelGGL(k_keys_in_order_hist<10>, grid, block, 0, s, keys0, R, disorder, plan.cell_bits, plan.buckets, range, hist);
+    } else {
+        hipLaunchKernelGGL(k_keys_in_order, dim3((uint32_t)((R + 1023) / 1024)), block, 0, s,
+                           keys0, R, disorder, plan.cell_bits, plan.buckets, range);
+    }
+    prof_end(K_ORDER_CHECK, s);
     for (int pass = 0; pass < plan.passes; pass++) {
         uint32_t* kout = (pass & 1) ? keys0 : keys1;
         uint32_t* vout = (pass & 1) ? vals0 : vals1;
         const int shift = plan.digit_shift[pass];
         const int D = std::max(8, plan.digit_bits[pass]);
-        const int64_t len = ((int64_t)1 << D) * plan.tiles;
-        const dim3 grid((uint32_t)plan.tiles), block(SORT_THREADS);
-        prof_begin(K_RADIX_HIST, s);
-        if (D == 8) hipLaunchKernelGGL(k_radix_hist<8>, grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-        else if (D == 9) hipLaunchKernelGGL(k_radix_hist<9>, grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-        else hipLaunchKernelGGL(k_radix_hist<10>, grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-        prof_end(K_RADIX_HIST, s);
-        launch_scan(hist, hoff, scanp, len, (len + SCAN_TILE - 1) / SCAN_TILE, s, disorder);
-        prof_begin(K_RADIX_SCATTER, s);
-        if (D == 8) hipLaunchKernelGGL(k_radix_scatter<8>, grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
-        else if (D == 9) hipLaunchKernelGGL(k_radix_scatter<9>, grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
-        else hipLaunchKernelGGL(k_radix_scatter<10>, grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
-        prof_end(K_RADIX_SCATTER, s);
+        if (small) {
+            if (pass > 0) {
+                prof_begin(K_RADIX_HIST, s);
+                if (D == 8) hipLaunchKernelGGL((k_radix_hist<8, true>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
+                else if (D == 9) hipLaunchKernelGGL((k_radix_hist<9, true>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
+                else hipLaunchKernelGGL((k_radix_hist<10, true>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
+                prof_end(K_RADIX_HIST, s);
+            }
+            prof_begin(K_RADIX_SCATTER, s);
+            if (D == 8) hipLaunchKernelGGL((k_radix_scatter<8, true>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hist, plan.tiles, disorder);
+            else if (D == 9) hipLaunchKernelGGL((k_radix_scatter<9, true>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hist, plan.tiles, disorder);
+            else hipLaunchKernelGGL((k_radix_scatter<10, true>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hist, plan.tiles, disorder);
+            prof_end(K_RADIX_SCATTER, s);
+        } else {
+            const int64_t len = ((int64_t)1 << D) * plan.tiles;
+            prof_begin(K_RADIX_HIST, s);
+            if (D == 8) hipLaunchKernelGGL((k_radix_hist<8, false>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
+            else if (D == 9) hipLaunchKernelGGL((k_radix_hist<9, false>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
+            else hipLaunchKernelGGL((k_radix_hist<10, false>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
+            prof_end(K_RADIX_HIST, s);
+            launch_scan(hist, hoff, scanp, len, (len + SCAN_TILE - 1) / SCAN_TILE, s, disorder);
+            prof_begin(K_RADIX_SCATTER, s);
+            if (D == 8) hipLaunchKernelGGL((k_radix_scatter<8, false>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
+            else if (D == 9) hipLaunchKernelGGL((k_radix_scatter<9, false>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
+            else hipLaunchKernelGGL((k_radix_scatter<10, false>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
+            prof_end(K_RADIX_SCATTER, s);
+        }
         kin = kout;
         vin = vout;
     }
     *skeys_out = kin;
     *svals_out = vin;
-}
-
-// Whether the R keys in keys0 are in order: the workspace's disorder word
-// is cleared, then set by any descent.  With `range` (zero-filled before) the
-// check also writes the bucket ranges the keys give if they are in order.
-static uint32_t* launch_order_check(const BwdPlan& plan, void* ws, int2* range, hipStream_t s) {
-    char* wsb = (char*)ws;
-    const uint32_t* keys0 = (const uint32_t*)(wsb + plan.off_keys0);
-    uint32_t* disorder = (uint32_t*)(wsb + plan.off_disorder);
-    const int64_t R = plan.records;
-    uint32_t* flags = disorder + ORDER_FLAGS_AT;
-    launch_fill(disorder, 1, 0u, s);
-    if (R > 0) {
-        const int64_t nflags = (R + 1023) / 1024;
-        prof_begin(K_ORDER_CHECK, s);
-        hipLaunchKernelGGL(k_keys_in_order, dim3((uint32_t)nflags), dim3(256), 0, s, keys0, R,
-                           flags, plan.cell_bits, plan.buckets, range);
-        hipLaunchKernelGGL(k_flags_any, dim3((uint32_t)((nflags + 4095) / 4096)), dim3(256), 0, s,
-                           flags, nflags, disorder);
-        prof_end(K_ORDER_CHECK, s);
-    }
     return disorder;
 }
 
 hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, const TileOut& out,
-                             const BwdPlan& plan, void* ws, hipStream_t s) {
+                             const BwdPlan& plan, void* ws, bool cleared, hipStream_t s) {
     char* wsb = (char*)ws;
     uint32_t* keys0 = (uint32_t*)(wsb + plan.off_keys0);
     float* wrec = (float*)(wsb + plan.off_wrec);
@@ -1787,27 +1884,24 @@ hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, cons
     // 2. sort, skipped on the device when the records were made in key order
     // (the order check then also writes the bucket ranges)
     const int64_t nb = plan.buckets;
-    launch_fill(big_count, BIG_LISTS * BIG_STRIDE + nb * 2, 0u, s);  // counters and ranges
+    if (!cleared)  // the disorder word, the counters and the ranges
+        launch_fill((uint32_t*)(wsb + plan.off_disorder), (int64_t)(plan.clear_bytes / 4), 0u, s);
     const uint32_t* skeys = keys0;
     const uint32_t* svals = nullptr;
     const uint32_t* dis = nullptr;
-    if (R > 0) {
-        dis = launch_order_check(plan, ws, range, s);
-        launch_sort_records(plan, ws, dis, s, &skeys, &svals);
-    }
+    if (R > 0) dis = launch_sort_records(plan, ws, range, s, &skeys, &svals);
 
-    // 3. ranges of sorted records (returns at once when the sort did)
-    if (R > 0) {
+    // 3. ranges of the sorted records, with the records' payload in sorted
+    // order when buckets hold 64 records or fewer on average (most records
+    // then go through the register window); both return at once when the sort
+    // did
+    const bool pay = R > 0 && R <= 64 * nb;
+    if (R > 0 && !pay) {
         prof_begin(K_BUCKET_RANGES, s);
         hipLaunchKernelGGL(k_bucket_ranges, dim3((uint32_t)((R + 1023) / 1024)), dim3(256), 0, s,
                            skeys, R, plan.cell_bits, nb, range, dis);
         prof_end(K_BUCKET_RANGES, s);
     }
-
-    // 4. the records' payload in sorted order (when buckets hold 64 records or
-    // fewer on average: most records then go through the register window;
-    // not written when the records came in order), then pass 1 over buckets
-    const bool pay = R > 0 && R <= 64 * nb;
     if (pay) {
         const int64_t per_block = 256 * PAYLOAD_PER_THREAD;
         const dim3 gp((uint32_t)((R + per_block - 1) / per_block));
@@ -1837,27 +1931,24 @@ hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, cons
     prof_end(K_SEGACC, s);
     if (R > 64) {
         // BIG_LISTS x parts workgroups, four wavefronts each; parts grows with
-        // the number of buckets that can be big
+        // the number of buckets that can be big.  Buckets with more than PIECE
+        // records: one wavefront per chunk in the same launch, then combined.
         const int64_t parts = std::min<int64_t>(std::max<int64_t>(
             1, (R / 65 + 4 * BIG_LISTS - 1) / (4 * BIG_LISTS)), 64);
-        const dim3 g2((uint32_t)(BIG_LISTS * parts));
+        const uint32_t big_blocks = (uint32_t)(BIG_LISTS * parts);
+        const uint32_t hot_blocks = R > PIECE ? (uint32_t)((plan.chunks + 3) / 4) : 0u;
+        const dim3 g2(big_blocks + hot_blocks);
         prof_begin(K_SEGACC_BIG, s);
         if (mode == MODE_NEAREST)
-            launch_segacc_big_c<MODE_NEAREST>(C, g2, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, range, out, n, cell_mask, big_count, big_list, plan.big_cap, keys0, dis);
+            launch_segacc_big_c<MODE_NEAREST>(C, g2, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, range, out, n, plan.cell_bits, big_count, big_list, plan.big_cap, big_blocks, part, R, nb, keys0, dis);
         else
-            launch_segacc_big_c<MODE_BILINEAR>(C, g2, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, range, out, n, cell_mask, big_count, big_list, plan.big_cap, keys0, dis);
+            launch_segacc_big_c<MODE_BILINEAR>(C, g2, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, range, out, n, plan.cell_bits, big_count, big_list, plan.big_cap, big_blocks, part, R, nb, keys0, dis);
         prof_end(K_SEGACC_BIG, s);
     }
 
-    // 5. pass 2 for buckets with more than PIECE records
+    // 5. the chunks of buckets with more than PIECE records
     if (R > PIECE) {
         const dim3 g2((uint32_t)plan.chunks);
-        prof_begin(K_SEGACC_HOT, s);
-        if (mode == MODE_NEAREST)
-            launch_segacc_hot_c<MODE_NEAREST>(C, g2, (size_t)te * 4, s, skeys, svals, wrec, grad_out, range, part, R, n, plan.cell_bits, nb, keys0, dis, big_count + HOT_FLAG);
-        else
-            launch_segacc_hot_c<MODE_BILINEAR>(C, g2, (size_t)te * 4, s, skeys, svals, wrec, grad_out, range, part, R, n, plan.cell_bits, nb, keys0, dis, big_count + HOT_FLAG);
-        prof_end(K_SEGACC_HOT, s);
         prof_begin(K_COMBINE_HOT, s);
         hipLaunchKernelGGL(k_combine_hot, g2, dim3(64), 0, s, skeys, range, part, out, R, te,
                            plan.cell_bits, nb, keys0, dis, big_count + HOT_FLAG);
@@ -1880,7 +1971,9 @@ __global__ __launch_bounds__(256) void k_plan_keys(int W, int H, int n,
                                                    const float* __restrict__ tbn,
                                                    const float* __restrict__ view,
                                                    uint32_t* __restrict__ keys, FragMap m,
-                                                   int cell_bits) {
+                                                   int cell_bits,
+                                                   uint32_t* __restrict__ disorder) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *disorder = 0u;  // for the order check
     const int64_t f = frag_of(m, blockIdx.x, gridDim.x, threadIdx.x);
     if (f < 0) return;
     const Frag g = load_frag(uv, tbn, view, f);
@@ -1970,17 +2063,17 @@ hipError_t launch_plan(const TexView& t, int mode, const float* uv, const float*
     const int64_t N = m.N;
     if (N <= 0) return hipSuccess;
     uint32_t* keys0 = (uint32_t*)((char*)ws + plan.off_keys0);
+    uint32_t* disorder = (uint32_t*)((char*)ws + plan.off_disorder);
     prof_begin(K_PLAN_KEYS, s);
     if (mode == MODE_NEAREST)
         hipLaunchKernelGGL(k_plan_keys<MODE_NEAREST>, dim3(fragmap_blocks(m)), dim3(256), 0, s,
-                           t.W, t.H, t.n, uv, tbn, view, keys0, m, plan.cell_bits);
+                           t.W, t.H, t.n, uv, tbn, view, keys0, m, plan.cell_bits, disorder);
     else
         hipLaunchKernelGGL(k_plan_keys<MODE_BILINEAR>, dim3(fragmap_blocks(m)), dim3(256), 0, s,
-                           t.W, t.H, t.n, uv, tbn, view, keys0, m, plan.cell_bits);
+                           t.W, t.H, t.n, uv, tbn, view, keys0, m, plan.cell_bits, disorder);
     prof_end(K_PLAN_KEYS, s);
-    const uint32_t* dis = launch_order_check(plan, ws, nullptr, s);
     const uint32_t *skeys = nullptr, *svals = nullptr;
-    launch_sort_records(plan, ws, dis, s, &skeys, &svals);
+    const uint32_t* dis = launch_sort_records(plan, ws, nullptr, s, &skeys, &svals);
     prof_begin(K_PLAN_GATHER, s);
     hipLaunchKernelGGL(k_plan_gather, dim3((uint32_t)((N + 255) / 256)), dim3(256), 0, s, svals,
                        N, uv, tbn, view, order, uv_out, tbn_out, view_out, dis);
@@ -1992,12 +2085,13 @@ template <int FMT, int MODE>
 static void launch_lod_frag_c(int C, dim3 grid, hipStream_t s, const LevelSet& ls,
                               const float* uv, const float* tbn, const float* view,
                               const float* duv, const float* go, const LevelStarts& st, float* gview, float* guv, uint32_t* keys,
-                              float* wrec, float* gl, const FragMap& m, int cb, uint32_t sent) {
+                              float* wrec, float* gl, const FragMap& m, int cb, uint32_t sent,
+                              const ClearWords& clear) {
     switch (C) {
-    case 1: hipLaunchKernelGGL((k_lod_bwd_fragment<FMT, 1, MODE>), grid, dim3(256), 0, s, ls, uv, tbn, view, duv, go, st, gview, guv, keys, wrec, gl, m, cb, sent); break;
-    case 2: hipLaunchKernelGGL((k_lod_bwd_fragment<FMT, 2, MODE>), grid, dim3(256), 0, s, ls, uv, tbn, view, duv, go, st, gview, guv, keys, wrec, gl, m, cb, sent); break;
-    case 3: hipLaunchKernelGGL((k_lod_bwd_fragment<FMT, 3, MODE>), grid, dim3(256), 0, s, ls, uv, tbn, view, duv, go, st, gview, guv, keys, wrec, gl, m, cb, sent); break;
-    default: hipLaunchKernelGGL((k_lod_bwd_fragment<FMT, 4, MODE>), grid, dim3(256), 0, s, ls, uv, tbn, view, duv, go, st, gview, guv, keys, wrec, gl, m, cb, sent); break;
+    case 1: hipLaunchKernelGGL((k_lod_bwd_fragment<FMT, 1, MODE>), grid, dim3(256), 0, s, ls, uv, tbn, view, duv, go, st, gview, guv, keys, wrec, gl, m, cb, sent, clear); break;
+    case 2: hipLaunchKernelGGL((k_lod_bwd_fragment<FMT, 2, MODE>), grid, dim3(256), 0, s, ls, uv, tbn, view, duv, go, st, gview, guv, keys, wrec, gl, m, cb, sent, clear); break;
+    case 3: hipLaunchKernelGGL((k_lod_bwd_fragment<FMT, 3, MODE>), grid, dim3(256), 0, s, ls, uv, tbn, view, duv, go, st, gview, guv, keys, wrec, gl, m, cb, sent, clear); break;
+    default: hipLaunchKernelGGL((k_lod_bwd_fragment<FMT, 4, MODE>), grid, dim3(256), 0, s, ls, uv, tbn, view, duv, go, st, gview, guv, keys, wrec, gl, m, cb, sent, clear); break;
     }
 }
 
@@ -2005,20 +2099,23 @@ hipError_t launch_lod_bwd_fragment(const LevelSet& ls, int fmt, int mode, const 
                                    const float* tbn, const float* view, const float* duv,
                                    const float* grad_out, const int64_t* start, float* grad_view, float* grad_uv,
                                    uint32_t* keys, float* wrec, float* gl, const FragMap& m,
-                                   int cell_bits, uint32_t sentinel, hipStream_t s) {
+                                   const BwdPlan& plan, void* ws, bool* cleared, hipStream_t s) {
     LevelStarts st{};
     for (int l = 0; l <= ls.levels && l <= MAX_LEVELS; l++) st.v[l] = start[l];
     const dim3 grid(fragmap_blocks(m));
     const int C = ls.C;
+    ClearWords clear{nullptr, 0};
+    if (keys) clear = clear_in_launch(plan, ws, grid.x);
+    *cleared = clear.quads > 0;
     prof_begin(K_LOD_BWD_FRAGMENT, s);
     if (mode == MODE_NEAREST) {
-        if (fmt == FMT_F32) launch_lod_frag_c<FMT_F32, MODE_NEAREST>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, cell_bits, sentinel);
-        else if (fmt == FMT_BF16) launch_lod_frag_c<FMT_BF16, MODE_NEAREST>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, cell_bits, sentinel);
-        else launch_lod_frag_c<FMT_FP8, MODE_NEAREST>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, cell_bits, sentinel);
+        if (fmt == FMT_F32) launch_lod_frag_c<FMT_F32, MODE_NEAREST>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, plan.cell_bits, plan.sentinel, clear);
+        else if (fmt == FMT_BF16) launch_lod_frag_c<FMT_BF16, MODE_NEAREST>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, plan.cell_bits, plan.sentinel, clear);
+        else launch_lod_frag_c<FMT_FP8, MODE_NEAREST>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, plan.cell_bits, plan.sentinel, clear);
     } else {
-        if (fmt == FMT_F32) launch_lod_frag_c<FMT_F32, MODE_BILINEAR>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, cell_bits, sentinel);
-        else if (fmt == FMT_BF16) launch_lod_frag_c<FMT_BF16, MODE_BILINEAR>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, cell_bits, sentinel);
-        else launch_lod_frag_c<FMT_FP8, MODE_BILINEAR>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, cell_bits, sentinel);
+        if (fmt == FMT_F32) launch_lod_frag_c<FMT_F32, MODE_BILINEAR>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, plan.cell_bits, plan.sentinel, clear);
+        else if (fmt == FMT_BF16) launch_lod_frag_c<FMT_BF16, MODE_BILINEAR>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, plan.cell_bits, plan.sentinel, clear);
+        else launch_lod_frag_c<FMT_FP8, MODE_BILINEAR>(C, grid, s, ls, uv, tbn, view, duv, grad_out, st, grad_view, grad_uv, keys, wrec, gl, m, plan.cell_bits, plan.sentinel, clear);
     }
     prof_end(K_LOD_BWD_FRAGMENT, s);
     return hipGetLastError();

@@ -26,7 +26,6 @@ enum KernelId {
     K_RADIX_SCATTER,
     K_BUCKET_RANGES,
     K_SEGACC,
-    K_SEGACC_HOT,
     K_COMBINE_HOT,
     K_SEGACC_BIG,
     K_BAKE_DIRECTIONS,
@@ -134,8 +133,10 @@ struct BwdPlan {
     // workspace offsets (bytes); the sort's buffers and the disorder word
     // come first and end at sort_total
     size_t off_keys0, off_keys1, off_vals0, off_vals1, off_hist, off_hoff, off_scanp,
-        off_disorder, sort_total, off_wrec, off_payf, off_payg, off_range, off_biglist,
+        off_disorder, sort_total, off_range, off_wrec, off_payf, off_payg, off_biglist,
         off_part, total;
+    size_t clear_bytes;   // cleared before the order check: the disorder word, the
+                          // big-bucket counters, the ranges (from off_disorder on)
 };
 constexpr int PIECE = 2048;  // records per chunk; buckets with more are "hot"
 constexpr int SEG_GROUP = 8;  // buckets per wavefront in the first accumulation pass
@@ -143,7 +144,7 @@ constexpr int BIG_LISTS = 64; // big-bucket lists, each with its own counter
 constexpr int BIG_STRIDE = 64;  // u32 between two counters (256 bytes)
 constexpr int HOT_FLAG = 1;     // u32 after counter 0: set when a bucket needs pass 2
 constexpr int PAYLOAD_PER_THREAD = 4;  // sorted records per thread in the payload launch
-constexpr int ORDER_FLAGS_AT = 64;  // u32 after the disorder word where the order flags start
+constexpr int SMALL_SORT_TILES = 64;  // sorts of up to this many tiles make fewer launches
 constexpr int BIG_RUN = 64;     // consecutive groups that append to one list
 // sparse: fragments whose upstream gradient is all zero make no records (their
 // keys sort past every bucket and are skipped), at the price of one key bit.
@@ -162,9 +163,10 @@ struct TileOut {
 
 // Steps after the per-fragment kernel: sort the records, find the bucket
 // ranges, write the sorted payload, accumulate the tiles into `out`.
-// grad_out: the upstream gradient of the records' fragments (units).
+// grad_out: the upstream gradient of the records' fragments (units).  cleared:
+// the per-fragment launch cleared the plan's clear_bytes.
 hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, const TileOut& out,
-                             const BwdPlan& plan, void* ws, hipStream_t s);
+                             const BwdPlan& plan, void* ws, bool cleared, hipStream_t s);
 
 // Backward of the level-of-detail lookup in one pass: every fragment makes
 // records on the (one or two) levels it blends, in the chain's bucket
@@ -186,7 +188,7 @@ hipError_t launch_lod_bwd_fragment(const LevelSet& ls, int fmt, int mode, const 
                                    const float* grad_out, const int64_t* start,
                                    float* grad_view, float* grad_uv,
                                    uint32_t* keys, float* wrec, float* gl, const FragMap& m,
-                                   int cell_bits, uint32_t sentinel, hipStream_t s);
+                                   const BwdPlan& plan, void* ws, bool* cleared, hipStream_t s);
 hipError_t launch_mip_adjoint(const TexView& src, const float* grad_dst, float* grad_src,
                               hipStream_t s);
 
@@ -211,11 +213,6 @@ hipError_t launch_vq_assign(const float* x, int64_t M, int D, const float* codeb
                             int32_t* assign, float* dist, hipStream_t s);
 hipError_t launch_vq_update(const float* x, const int32_t* assign, float* codebook,
                             int32_t* counts, const VqPlan& plan, void* ws, hipStream_t s);
-
-// The stable sort of a plan's records (keys in the workspace's keys0); with
-// disorder non-NULL its launches return at once when that device word is 0.
-void launch_sort_records(const BwdPlan& plan, void* ws, const uint32_t* disorder, hipStream_t s,
-                         const uint32_t** skeys, const uint32_t** svals);
 
 // Visit plan: the fragments ordered by their nearest-mode record key (or the
 // key of their first bucket in the bilinear-bucket mode), stable in the

@@ -66,11 +66,12 @@ hipError_t launch_lookup_lod_bwd(const LevelSet& ls, int fmt, int mode, const fl
     float* gl = (float*)(base + lay.off_gl);
     uint32_t* keys = want ? (uint32_t*)(bws + plan.off_keys0) : nullptr;
     float* wrec = (float*)(bws + plan.off_wrec);
+    bool cleared = false;
     hipError_t e = launch_lod_bwd_fragment(ls, fmt, mode, uv, tbn, view, duv, grad_out,
                                            out.start, grad_view, grad_uv, keys, wrec, gl, m,
-                                           plan.cell_bits, plan.sentinel, s);
+                                           plan, bws, &cleared, s);
     if (e != hipSuccess || !want) return e;
-    return launch_accumulate(ls.n, ls.C, mode, gl, out, plan, bws, s);
+    return launch_accumulate(ls.n, ls.C, mode, gl, out, plan, bws, cleared, s);
 }
 
 // grad_src (level l, W x H buckets of E values) += adjoint of the chain step
