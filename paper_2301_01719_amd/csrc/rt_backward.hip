@@ -26,8 +26,8 @@
 //                       added to the texels of the cell in four ordered phases
 //                       in LDS, and the n x n x C tile is written once.
 //                       Untouched buckets get zeros.  Buckets with 65..PIECE
-//                       records go to k_segacc_big (rounds of 64 with a
-//                       carry), more to pass 2.
+//                       records go to k_segacc_big (rounds of 64), more to
+//                       pass 2.
 //   5. k_segacc_big /   pass 2: hot buckets are cut at fixed chunk boundaries of
 //      k_combine_hot    the sorted records; each chunk's part is reduced as in
 //                       pass 1 into a partial tile, and the partials are summed
@@ -1024,70 +1024,125 @@ __device__ __forceinline__ void load_payg(const float* __restrict__ payg, int64_
     }
 }
 
-// One round of up to 64 sorted records of one bucket, one record per lane
-// (lanes without a record carry a cell no record has).  The four tap
-// contributions are summed per cell by an inclusive segmented scan across
-// lanes with a fixed shape.  `ends_here` tells whether a lane's cell ends in
-// this round; a cell that ends adds its four sums to its four texels in four
-// phases, so no two lanes touch one texel at once.
-template <int C>
-__device__ __forceinline__ void accumulate_tails(int cell, const float v[4 * C], bool tail, int n,
-                                                 float* tile);
-
-template <int C>
-__device__ __forceinline__ void accumulate_round(int cell, float v[4 * C], bool valid,
-                                                 bool next_same, int n, float* tile) {
-    const int lane = threadIdx.x & 63;
-    constexpr int F = 4 * C;
-    // a run of equal cells is contiguous, so once no lane has a partner at
-    // distance o every run is at most o long and the scan is complete
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int oc = lanes_up(cell, o);
-        const bool same = lane >= o && oc == cell;
-        if (__ballot(same) == 0ull) break;
-#pragma unroll
-        for (int q = 0; q < F; q++) {
-            const float ov = lanes_up(v[q], o);
-            if (same) v[q] += ov;
-        }
-    }
-    const bool tail = valid && !next_same;
-    accumulate_tails<C>(cell, v, tail, n, tile);
+// Row of a cell (cell / n) without a division: exact for cell < n * n, n <= 64
+// with row_inv = ceil(2^20 / n), because then cell * (row_inv * n - 2^20) < 2^20.
+__device__ __forceinline__ uint32_t row_inverse(int n) {
+    return ((1u << 20) + (uint32_t)n - 1u) / (uint32_t)n;
 }
 
+// Adds C channel sums to texel `t` of the tile in one LDS access each way.
 template <int C>
-__device__ __forceinline__ void accumulate_tails(int cell, const float v[4 * C], bool tail, int n,
-                                                 float* tile) {
-    if (__ballot(tail) == 0ull) return;
-    int y0 = 0, x0 = 0, x1 = 0, y1 = 0;
-    if (tail) {
-        y0 = cell / n;
-        x0 = cell - y0 * n;
-        x1 = min(x0 + 1, n - 1);
-        y1 = min(y0 + 1, n - 1);
-    }
-    wave_lds_sync();
-    if (tail) {
+__device__ __forceinline__ void texel_add(float* tile, int t, const float v[C]) {
+    if constexpr (C == 4) {
+        f4v* p = (f4v*)tile + t;
+        const f4v a = {v[0], v[1], v[2], v[3]};
+        *p += a;
+    } else if constexpr (C == 2) {
+        float2* p = (float2*)tile + t;
+        float2 q = *p;
+        q.x += v[0];
+        q.y += v[1];
+        *p = q;
+    } else {
 #pragma unroll
-        for (int c = 0; c < C; c++) tile[(y0 * n + x0) * C + c] += v[0 * C + c];
+        for (int c = 0; c < C; c++) tile[t * C + c] += v[c];
+    }
+}
+
+// The lanes with `on` set, no two of them with the same cell, add their four
+// sums to their cell's four texels in four phases, so no two lanes touch one
+// texel at once.
+template <int C>
+__device__ __forceinline__ void accumulate_tails(int cell, const float v[4 * C], bool on, int n,
+                                                 uint32_t row_inv, float* tile) {
+    if (__ballot(on) == 0ull) return;
+    int t00 = 0, dx = 0, dy = 0;
+    if (on) {
+        const int y0 = (int)(((uint32_t)cell * row_inv) >> 20);
+        const int x0 = cell - y0 * n;
+        t00 = cell;
+        dx = x0 + 1 < n ? 1 : 0;
+        dy = y0 + 1 < n ? n : 0;
     }
     wave_lds_sync();
-    if (tail) {
+    if (on) texel_add<C>(tile, t00, v);
+    wave_lds_sync();
+    if (on) texel_add<C>(tile, t00 + dx, v + C);
+    wave_lds_sync();
+    if (on) texel_add<C>(tile, t00 + dy, v + 2 * C);
+    wave_lds_sync();
+    if (on) texel_add<C>(tile, t00 + dx + dy, v + 3 * C);
+    wave_lds_sync();
+}
+
+// One round of up to 64 sorted records of one bucket, one record per lane
+// (lanes without a record carry a cell no record has), added to the tile.
+// Records of one cell are a run of neighbouring lanes.  Runs are cut into
+// blocks of BLOCK = 4, each block is summed by two segmented steps of DPP
+// shifts, and the blocks' last lanes add to the tile, the blocks of a run one
+// after the other.  Against a scan over whole runs that takes no step through
+// the LDS crossbar and no carry between rounds: a bucket of 65..2048 records
+// meets runs of a few records (its cells are spread by the normals and the
+// views), where the scan's steps at distances 4 and up and the carry were a
+// third of the vector instructions and two thirds of the LDS ones.  The LDS
+// round trips of a block cost about as much as a step, so when a run reaches
+// more than LONG_RUN records (two blocks) the round scans whole runs instead
+// (64 views: 785 us with 8, 819 with 16; both keep the sums of a run in a tree).
+constexpr int BLOCK = 4, LONG_RUN = 8;
+
+template <int C>
+__device__ __forceinline__ void accumulate_round(int cell, float v[4 * C], bool valid, int n,
+                                                 uint32_t row_inv, float* tile) {
+    const int lane = threadIdx.x & 63;
+    constexpr int F = 4 * C;
+    const int below = lanes_up(cell, 1);  // by every lane: a shift reads active lanes only
+    const uint64_t heads = __ballot(lane == 0 || below != cell);
+    const uint64_t upto = heads & (~0ull >> (63 - lane));  // lane 0 is a head: never 0
+    const int rank = lane - (63 - __builtin_clzll(upto));
+    uint64_t firsts;  // lanes that start a summed piece
+    int piece;        // its number in its run
+    if (__ballot(rank >= LONG_RUN) != 0ull) {
+        // a run is contiguous, so once no lane has a partner at distance o
+        // every run is at most o long and the scan is complete
 #pragma unroll
-        for (int c = 0; c < C; c++) tile[(y0 * n + x1) * C + c] += v[1 * C + c];
-    }
-    wave_lds_sync();
-    if (tail) {
+        for (int o = 1; o < 64; o <<= 1) {
+            const bool same = rank >= o;
+            if (__ballot(same) == 0ull) break;
 #pragma unroll
-        for (int c = 0; c < C; c++) tile[(y1 * n + x0) * C + c] += v[2 * C + c];
-    }
-    wave_lds_sync();
-    if (tail) {
+            for (int q = 0; q < F; q++) {
+                const float ov = lanes_up(v[q], o);
+                if (same) v[q] += ov;
+            }
+        }
+        firsts = heads;
+        piece = 0;
+    } else {
+        const int at = rank & (BLOCK - 1);
+        const uint64_t rest = __ballot(at != 0);
+        if (rest != 0ull) {
 #pragma unroll
-        for (int c = 0; c < C; c++) tile[(y1 * n + x1) * C + c] += v[3 * C + c];
+            for (int q = 0; q < F; q++) {
+                const float ov = lanes_up(v[q], 1);
+                if (at >= 1) v[q] += ov;
+            }
+            if (__ballot(at >= 2) != 0ull) {
+#pragma unroll
+                for (int q = 0; q < F; q++) {
+                    const float ov = lanes_up(v[q], 2);
+                    if (at >= 2) v[q] += ov;
+                }
+            }
+        }
+        firsts = ~rest;
+        piece = rank / BLOCK;
     }
-    wave_lds_sync();
+    const uint64_t lasts = (firsts >> 1) | (1ull << 63);
+    const bool last = valid && ((lasts >> lane) & 1ull) != 0ull;
+    for (int p = 0;; p++) {
+        const bool on = last && piece == p;
+        if (__ballot(on) == 0ull) break;
+        accumulate_tails<C>(cell, v, on, n, row_inv, tile);
+    }
 }
 
 // A sorted record as loaded: its key, its bilinear fractions and its upstream
@@ -1140,60 +1195,6 @@ __device__ __forceinline__ void expand_raw(const RawRec<C>& r, float v[4 * C]) {
         v[1 * C + c] = w01 * gc;
         v[2 * C + c] = w10 * gc;
         v[3 * C + c] = w11 * gc;
-    }
-}
-
-// Reduce sorted records [a, e) (all of one bucket) into the wave's LDS tile
-// (zeroed by the caller), in rounds of 64 records.  A cell that runs past a
-// round carries its partial sum into the next round's first lane.  Each
-// round's records are loaded while the round before is summed.
-template <int C, int MODE>
-__device__ __forceinline__ void reduce_records(const uint32_t* __restrict__ skeys,
-                                               const uint32_t* __restrict__ svals,
-                                               const float* __restrict__ wrec,
-                                               const float* __restrict__ grad_out, int64_t a,
-                                               int64_t e, int n, uint32_t cell_mask,
-                                               float* tile) {
-    const int lane = threadIdx.x & 63;
-    constexpr int F = 4 * C;
-    float carry[F];
-#pragma unroll
-    for (int q = 0; q < F; q++) carry[q] = 0.f;
-    int carry_cell = -1;
-    RawRec<C> cur{}, nxt{};
-    if (a + lane < e) load_raw<C, MODE>(skeys, svals, wrec, grad_out, a + lane, cur);
-    for (int64_t base = a; base < e; base += 64) {
-        const int64_t i = base + lane;
-        const bool valid = i < e;
-        if (i + 64 < e) load_raw<C, MODE>(skeys, svals, wrec, grad_out, i + 64, nxt);
-        int cell = -2 - lane;  // distinct from every real cell and from each other
-        float v[F];
-#pragma unroll
-        for (int q = 0; q < F; q++) v[q] = 0.f;
-        if (valid) {
-            cell = (int)(cur.key & cell_mask);
-            expand_raw<C>(cur, v);
-        }
-        if (lane == 0 && cell == carry_cell) {
-#pragma unroll
-            for (int q = 0; q < F; q++) v[q] = carry[q] + v[q];
-        }
-        const int next_cell = lane_above(cell);
-        bool next_same = valid && lane < 63 && i + 1 < e && next_cell == cell;
-        bool spills = false;
-        // record i + 1 of lane 63 is the next round's first
-        const uint32_t key_after = __shfl(nxt.key, 0, 64);
-        if (valid && lane == 63 && i + 1 < e) spills = (int)(key_after & cell_mask) == cell;
-        // the scan runs before the carry is taken from lane 63
-        accumulate_round<C>(cell, v, valid, next_same || spills, n, tile);
-        if (__ballot(spills) != 0ull) {
-#pragma unroll
-            for (int q = 0; q < F; q++) carry[q] = __shfl(v[q], 63, 64);
-            carry_cell = __shfl(cell, 63, 64);
-        } else {
-            carry_cell = -1;
-        }
-        cur = nxt;
     }
 }
 
@@ -1351,13 +1352,13 @@ __device__ __forceinline__ void zero_store(float* __restrict__ dst, int te) {
 // sorted payload (shorter groups spread the buckets over more wavefronts once
 // the window loads are cheap).  k_segacc writes the untouched buckets and those with at most 64
 // records (served from one register window) and lists those with 65..PIECE
-// records for k_segacc_big (rounds of 64 with a carry).  Splitting keeps the
+// records for k_segacc_big (rounds of 64).  Splitting keeps the
 // register footprint of the common case small.  The list is split over
 // BIG_LISTS counters, one atomic per group, so that workloads where most
-// buckets are big do not serialise on one address: runs of BIG_RUN groups
-// take the lists in turn (group g appends to list (g / BIG_RUN) mod
-// BIG_LISTS), which keeps neighbouring buckets on one XCD in k_segacc_big.
-// The order inside a list does not matter, each bucket is reduced alone.
+// buckets are big do not serialise on one address: runs of 2^big_run_log
+// groups (at most BIG_RUN, see launch_accumulate) take the lists in turn,
+// which keeps neighbouring buckets on one XCD in k_segacc_big.  The order
+// inside a list does not matter, each bucket is reduced alone.
 template <int C, int MODE, int G>
 __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ skeys,
                                                 const uint32_t* __restrict__ svals,
@@ -1370,7 +1371,7 @@ __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ ske
                                                 int64_t R, int n, uint32_t cell_mask,
                                                 uint32_t* __restrict__ big_count,
                                                 uint32_t* __restrict__ big_list,
-                                                int64_t big_cap,
+                                                int64_t big_cap, int big_run_log,
                                                 const uint32_t* __restrict__ keys_made,
                                                 const uint32_t* __restrict__ disorder) {
     if (sort_skipped(disorder)) {
@@ -1382,6 +1383,7 @@ __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ ske
     const int te = n * n * C;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     float* tile = lds + w * te;
+    const uint32_t row_inv = row_inverse(n);
     const int64_t ngroups = (nbuckets + G - 1) / G;
     for (int64_t grp = (int64_t)xcd_block_id(blockIdx.x, gridDim.x) * 4 + w; grp < ngroups;
          grp += (int64_t)gridDim.x * 4) {
@@ -1396,7 +1398,7 @@ __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ ske
         // a bucket for pass 2: raise the flag that lets its kernels run
         if (__ballot(cl > PIECE) != 0ull && lane == 0) atomicOr(big_count + HOT_FLAG, 1u);
         if (bm != 0ull) {
-            const int64_t list = (grp / BIG_RUN) % BIG_LISTS;
+            const int64_t list = (grp >> big_run_log) & (BIG_LISTS - 1);
             uint32_t base = 0;
             if (lane == 0) base = atomicAdd(big_count + list * BIG_STRIDE, (uint32_t)__popcll(bm));
             base = __shfl(base, 0, 64);
@@ -1427,7 +1429,7 @@ __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ ske
             }
             tile_zero(tile, te);
             const int64_t i = win.start + lane;
-            accumulate_tails<C>(win.cell, v, tail && i >= rx && i < ry, n, tile);
+            accumulate_tails<C>(win.cell, v, tail && i >= rx && i < ry, n, row_inv, tile);
             tile_store(tile, dst, te);
         }
     }
@@ -1435,13 +1437,19 @@ __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ ske
 
 // Buckets with 65..PIECE records, listed by k_segacc (the first big_blocks
 // workgroups): workgroup x serves list x mod BIG_LISTS, one wavefront per
-// listed bucket, rounds of 64 records with a carry.
+// listed bucket, in rounds of 64 records.
 //
 // The workgroups after them are pass 2a, one wavefront per fixed chunk of PIECE
 // sorted records: a hot bucket overlapping the chunk (only the chunk's first
 // or last bucket can be hot) gets a partial tile, slot 0 for the first bucket
 // and slot 1 for the last.  They return at once when k_segacc saw no such
 // bucket.
+//
+// Bound by vector issue (73% of the cycles on the 64 views' 67M records, 269
+// vector and 30 LDS instructions a round; 326 and 57, with six times the bank
+// conflicts, when rounds scanned whole runs and carried the last one): 64 views
+// 973 -> 718 us, 8 views with bilinear buckets (33.5M records, gathered)
+// 600 -> 520 us, 2867 buckets of 70 records 39 -> 10.5 us (their lists).
 template <int C, int MODE>
 __global__ __launch_bounds__(256) void k_segacc_big(const uint32_t* __restrict__ skeys,
                                                     const uint32_t* __restrict__ svals,
@@ -1465,55 +1473,102 @@ __global__ __launch_bounds__(256) void k_segacc_big(const uint32_t* __restrict__
     extern __shared__ float lds[];
     const int te = n * n * C;
     const uint32_t cell_mask = cell_bits >= 32 ? 0xFFFFFFFFu : ((1u << cell_bits) - 1u);
+    const uint32_t row_inv = row_inverse(n);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float* tile = lds + w * te;
+    // the wavefront's work items: entries [item, items) of its list in steps of
+    // `stride`, or the (at most two) slots of its chunk
+    uint32_t item, items, stride;
+    const uint32_t* entries = nullptr;
+    int c0 = 0, c1 = 0;
+    uint32_t b_next = 0, b_last = 0;
+    int2 r_next = make_int2(0, 0);
     if (!hot) {
         const uint32_t list = blockIdx.x % BIG_LISTS;
-        const uint32_t lpart = blockIdx.x / BIG_LISTS, parts = big_blocks / BIG_LISTS;
-        const uint32_t count = __builtin_amdgcn_readfirstlane(big_count[list * BIG_STRIDE]);
-        const uint32_t* entries = big_list + list * big_cap;
-        const uint32_t stride = parts * 4;
-        // the next listed bucket and its range are read while this one is summed
-        uint32_t e = lpart * 4 + w;
-        uint32_t b_next = 0;
-        int2 r_next = make_int2(0, 0);
-        if (e < count) {
-            b_next = __builtin_amdgcn_readfirstlane(entries[e]);
-            r_next = range[b_next];
-        }
-        for (; e < count; e += stride) {
+        stride = big_blocks / BIG_LISTS * 4;
+        item = blockIdx.x / BIG_LISTS * 4 + w;
+        items = __builtin_amdgcn_readfirstlane(big_count[list * BIG_STRIDE]);
+        entries = big_list + list * big_cap;
+        if (item < items) b_next = __builtin_amdgcn_readfirstlane(entries[item]);
+    } else {
+        const int64_t first = ((int64_t)(blockIdx.x - big_blocks) * 4 + w) * PIECE;
+        if (first >= R) return;
+        c0 = (int)first;
+        c1 = (int)((first + PIECE < R) ? first + PIECE : R);
+        b_next = __builtin_amdgcn_readfirstlane(skeys[c0]) >> cell_bits;
+        b_last = __builtin_amdgcn_readfirstlane(skeys[c1 - 1]) >> cell_bits;
+        // records past the last bucket (sparse plans) belong to no slot
+        stride = 1;
+        item = 0;
+        items = b_next >= nb ? 0u : b_last == b_next || b_last >= nb ? 1u : 2u;
+    }
+    if (item < items) r_next = range[b_next];
+    // the next item: `left` records of one bucket from record `at` on, their
+    // tile to dst.  Its successor's bucket and range are read ahead.
+    struct Item {
+        int at, left;
+        float* dst;
+    };
+    auto next_item = [&](Item& k) {
+        for (; item < items; item += stride) {
             const uint32_t b = b_next;
-            const int rx = __builtin_amdgcn_readfirstlane(r_next.x);
-            const int ry = __builtin_amdgcn_readfirstlane(r_next.y);
-            if (e + stride < count) {
-                b_next = __builtin_amdgcn_readfirstlane(entries[e + stride]);
+            int a = __builtin_amdgcn_readfirstlane(r_next.x);
+            int e = __builtin_amdgcn_readfirstlane(r_next.y);
+            if (item + stride < items) {
+                b_next = hot ? b_last : __builtin_amdgcn_readfirstlane(entries[item + stride]);
                 r_next = range[b_next];
             }
-            float* dst = tile_dst(out, b, te);
-            if (!dst) continue;
-            tile_zero(tile, te);
-            reduce_records<C, MODE>(skeys, svals, wrec, grad_out, rx, ry, n, cell_mask, tile);
-            tile_store(tile, dst, te);
+            if (hot) {
+                if (e - a <= PIECE) continue;
+                a = a > c0 ? a : c0;
+                e = e < c1 ? e : c1;
+                k.dst = part + (c0 / PIECE * 2 + (int64_t)item) * te;
+            } else {
+                k.dst = tile_dst(out, b, te);
+                if (!k.dst) continue;  // a level that is not written
+            }
+            k.at = a;
+            k.left = e - a;
+            item += stride;
+            return true;
         }
-        return;
-    }
-    const int64_t k = (int64_t)(blockIdx.x - big_blocks) * 4 + w;
-    const int64_t c0 = k * PIECE;
-    if (c0 >= R) return;
-    const int64_t c1 = (c0 + PIECE < R) ? c0 + PIECE : R;
-    const uint32_t bf = __builtin_amdgcn_readfirstlane(skeys[c0]) >> cell_bits;
-    const uint32_t bl = __builtin_amdgcn_readfirstlane(skeys[c1 - 1]) >> cell_bits;
-    for (int slot = 0; slot < 2; slot++) {
-        const uint32_t b = slot == 0 ? bf : bl;
-        if (slot == 1 && bl == bf) break;
-        if (b >= nb) break;  // the records past the last bucket (sparse plans)
-        const int2 r = range[b];
-        if ((int64_t)r.y - r.x <= PIECE) continue;
-        const int64_t a = r.x > c0 ? r.x : c0;
-        const int64_t e = r.y < c1 ? r.y : c1;
-        tile_zero(tile, te);
-        reduce_records<C, MODE>(skeys, svals, wrec, grad_out, a, e, n, cell_mask, tile);
-        tile_store(tile, part + (k * 2 + slot) * (int64_t)te, te);
+        return false;
+    };
+    // Rounds of 64 records.  The next round's records, of this bucket or of the
+    // next item, are loaded while this round is summed and before the tile is
+    // stored: on gfx950 one counter tracks a wavefront's loads and stores, so
+    // loads after the stores would wait for them.
+    Item cur_item, nxt_item{};
+    if (!next_item(cur_item)) return;
+    const int lane = threadIdx.x & 63;
+    RawRec<C> cur{}, nxt{};
+    if (lane < cur_item.left)
+        load_raw<C, MODE>(skeys, svals, wrec, grad_out, cur_item.at + lane, cur);
+    tile_zero(tile, te);
+    for (;;) {
+        const bool ends = cur_item.left <= 64;
+        bool more = true;
+        if (ends) {
+            more = next_item(nxt_item);
+        } else {
+            nxt_item.at = cur_item.at + 64;
+            nxt_item.left = cur_item.left - 64;
+            nxt_item.dst = cur_item.dst;
+        }
+        if (more && lane < nxt_item.left)
+            load_raw<C, MODE>(skeys, svals, wrec, grad_out, nxt_item.at + lane, nxt);
+        const bool valid = lane < cur_item.left;
+        float v[4 * C];
+        expand_raw<C>(cur, v);
+        const int cell = valid ? (int)(cur.key & cell_mask) : -2 - lane;
+        accumulate_round<C>(cell, v, valid, n, row_inv, tile);
+        if (ends) {
+            tile_store(tile, cur_item.dst, te);
+            if (!more) return;
+            tile_zero(tile, te);
+        }
+        cur = nxt;
+        cur_item = nxt_item;
     }
 }
 
@@ -1673,12 +1728,12 @@ static void launch_segacc_c(int C, dim3 grid, size_t shm, hipStream_t s, const u
                             const float* pf, const float* pg,
                             const int2* range, const TileOut& gt, int64_t nb, int64_t R, int n,
                             uint32_t mask, uint32_t* bc, uint32_t* bl, int64_t cap,
-                            const uint32_t* km, const uint32_t* dis) {
+                            int run_log, const uint32_t* km, const uint32_t* dis) {
     switch (C) {
-    case 1: hipLaunchKernelGGL((k_segacc<1, MODE, G>), grid, dim3(256), shm, s, sk, sv, wrec, go, pf, pg, range, gt, nb, R, n, mask, bc, bl, cap, km, dis); break;
-    case 2: hipLaunchKernelGGL((k_segacc<2, MODE, G>), grid, dim3(256), shm, s, sk, sv, wrec, go, pf, pg, range, gt, nb, R, n, mask, bc, bl, cap, km, dis); break;
-    case 3: hipLaunchKernelGGL((k_segacc<3, MODE, G>), grid, dim3(256), shm, s, sk, sv, wrec, go, pf, pg, range, gt, nb, R, n, mask, bc, bl, cap, km, dis); break;
-    default: hipLaunchKernelGGL((k_segacc<4, MODE, G>), grid, dim3(256), shm, s, sk, sv, wrec, go, pf, pg, range, gt, nb, R, n, mask, bc, bl, cap, km, dis); break;
+    case 1: hipLaunchKernelGGL((k_segacc<1, MODE, G>), grid, dim3(256), shm, s, sk, sv, wrec, go, pf, pg, range, gt, nb, R, n, mask, bc, bl, cap, run_log, km, dis); break;
+    case 2: hipLaunchKernelGGL((k_segacc<2, MODE, G>), grid, dim3(256), shm, s, sk, sv, wrec, go, pf, pg, range, gt, nb, R, n, mask, bc, bl, cap, run_log, km, dis); break;
+    case 3: hipLaunchKernelGGL((k_segacc<3, MODE, G>), grid, dim3(256), shm, s, sk, sv, wrec, go, pf, pg, range, gt, nb, R, n, mask, bc, bl, cap, run_log, km, dis); break;
+    default: hipLaunchKernelGGL((k_segacc<4, MODE, G>), grid, dim3(256), shm, s, sk, sv, wrec, go, pf, pg, range, gt, nb, R, n, mask, bc, bl, cap, run_log, km, dis); break;
     }
 }
 
@@ -1916,17 +1971,25 @@ hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, cons
     // lists of groups of 4: ceil(2x) <= 2 ceil(x) runs of half the buckets
     const int G = pay ? 4 : SEG_GROUP;
     const int64_t groups = (nb + G - 1) / G;
+    // Consecutive groups that append to one big-bucket list: BIG_RUN where that
+    // gives every list several runs, fewer for fewer groups, so that all lists
+    // (and with them all of the big pass's workgroups) get work.  With BIG_RUN
+    // throughout, the 2867 buckets of a 61 x 47 matrix went to 6 of the 64
+    // lists and the pass took 38 us.  Powers of two up to BIG_RUN keep the lists
+    // within the capacity planned for BIG_RUN.
+    int run_log = 0;
+    while ((2 << run_log) <= BIG_RUN && (groups >> (run_log + 1)) >= 4 * BIG_LISTS) run_log++;
     // the workgroups stride over the groups, so at most 2^20 of them keep the
     // launch within one dispatch (2^28 buckets and more at small n)
     const dim3 g1((uint32_t)std::min<int64_t>((groups + 3) / 4, int64_t(1) << 20));
     const float* pf = pay ? payf : nullptr;
     prof_begin(K_SEGACC, s);
     if (mode == MODE_NEAREST) {
-        if (pay) launch_segacc_c<MODE_NEAREST, 4>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, keys0, dis);
-        else launch_segacc_c<MODE_NEAREST, SEG_GROUP>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, keys0, dis);
+        if (pay) launch_segacc_c<MODE_NEAREST, 4>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
+        else launch_segacc_c<MODE_NEAREST, SEG_GROUP>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
     } else {
-        if (pay) launch_segacc_c<MODE_BILINEAR, 4>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, keys0, dis);
-        else launch_segacc_c<MODE_BILINEAR, SEG_GROUP>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, keys0, dis);
+        if (pay) launch_segacc_c<MODE_BILINEAR, 4>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
+        else launch_segacc_c<MODE_BILINEAR, SEG_GROUP>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
     }
     prof_end(K_SEGACC, s);
     if (R > 64) {
