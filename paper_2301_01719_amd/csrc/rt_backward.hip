@@ -42,7 +42,7 @@
 namespace rt {
 
 constexpr int SORT_THREADS = 256;
-constexpr int SORT_IPT = 16;
+constexpr int SORT_IPT = 16;  // keys per thread (4 or 8 in a small sort)
 constexpr int SORT_TILE = SORT_THREADS * SORT_IPT;  // 4096
 constexpr int SCAN_TILE = 4096;
 constexpr int64_t SCAN_FUSED_BLOCKS = 4096;
@@ -513,11 +513,11 @@ __global__ __launch_bounds__(256) void k_keys_in_order(const uint32_t* __restric
     if (range && !any && i0 < R) group_ranges(k, i0, R, cell_bits, nb, range);
 }
 
-// The order check of a small sort, on one radix tile of SORT_TILE keys per
+// The order check of a small sort, on one radix tile of 256 IPT keys per
 // workgroup, which also counts the first pass's digits of its tile (the key's
 // lowest D bits) into counts[tile][digit], so that pass needs no launch of
 // k_radix_hist.
-template <int D>
+template <int D, int IPT>
 __global__ __launch_bounds__(256) void k_keys_in_order_hist(const uint32_t* __restrict__ keys,
                                                             int64_t R,
                                                             uint32_t* __restrict__ disorder,
@@ -525,11 +525,11 @@ __global__ __launch_bounds__(256) void k_keys_in_order_hist(const uint32_t* __re
                                                             int2* __restrict__ range,
                                                             uint32_t* __restrict__ counts) {
     constexpr int B = 1 << D;
-    constexpr int GROUPS = SORT_TILE / 1024;
+    constexpr int GROUPS = IPT / 4;
     __shared__ uint32_t cnt[B];
     const int t = threadIdx.x;
     for (int d = t; d < B; d += 256) cnt[d] = 0;
-    const int64_t base = (int64_t)blockIdx.x * SORT_TILE + t * 4;
+    const int64_t base = (int64_t)blockIdx.x * (256 * IPT) + t * 4;
     uint32_t k[GROUPS][6];
     bool down = false;
 #pragma unroll
@@ -555,12 +555,12 @@ __global__ __launch_bounds__(256) void k_keys_in_order_hist(const uint32_t* __re
     for (int d = t; d < B; d += 256) counts[(int64_t)blockIdx.x * B + d] = cnt[d];
 }
 
-// Digit counts of one tile of SORT_TILE keys: hist[d * tiles + tile].  Tiles
+// Digit counts of one tile of 256 IPT keys: hist[d * tiles + tile].  Tiles
 // are renumbered so that each XCD takes a contiguous range: the counts of
 // neighbouring tiles share cache lines of the digit-major table, and so the
 // strided 4-byte stores of one XCD's tiles combine in its L2.  SMALL (a small
 // sort, whose scatter adds the counts up itself): tile-major, hist[tile * B + d].
-template <int D, bool SMALL>
+template <int D, bool SMALL, int IPT>
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(const uint32_t* __restrict__ keys,
                                                              int64_t R, int shift,
                                                              uint32_t* __restrict__ hist,
@@ -573,15 +573,15 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(const uint32_t* __r
     for (int d = t; d < B; d += SORT_THREADS) cnt[d] = 0;
     __syncthreads();
     const int64_t tile = xcd_block_id(blockIdx.x, gridDim.x);
-    const int64_t base = tile * SORT_TILE;
-    uint32_t k[SORT_IPT];
+    const int64_t base = tile * (SORT_THREADS * IPT);
+    uint32_t k[IPT];
 #pragma unroll
-    for (int r = 0; r < SORT_IPT; r++) {
+    for (int r = 0; r < IPT; r++) {
         const int64_t i = base + r * SORT_THREADS + t;
-        k[r] = i < R ? keys[i] : 0u;
+        k[r] = keys[i < R ? i : R - 1];
     }
 #pragma unroll
-    for (int r = 0; r < SORT_IPT; r++) {
+    for (int r = 0; r < IPT; r++) {
         const int64_t i = base + r * SORT_THREADS + t;
         if (i < R) atomicAdd(&cnt[(k[r] >> shift) & (B - 1)], 1u);
     }
@@ -747,57 +747,84 @@ __global__ __launch_bounds__(256) void k_scan_down(const uint32_t* __restrict__ 
     }
 }
 
+// Lanes of the wavefront holding the same D-bit digit (at bit `shift` of k) as
+// this one: one ballot per bit, and one three-input operation per half to keep
+// the lanes that agree in it (truth table of a & ~(b ^ c)).
+template <int D>
+__device__ __forceinline__ uint2 digit_peers(uint32_t k, int shift) {
+    uint2 peers = make_uint2(~0u, ~0u);
+#pragma unroll
+    for (int bit = 0; bit < D; bit++) {
+        const int on = (int)(k << (31 - shift - bit)) >> 31;  // the bit in all bits
+        const uint64_t m = __ballot(on != 0);
+        peers.x = __builtin_amdgcn_bitop3_b32(peers.x, (uint32_t)m, (uint32_t)on, 0x90);
+        peers.y = __builtin_amdgcn_bitop3_b32(peers.y, (uint32_t)(m >> 32), (uint32_t)on, 0x90);
+    }
+    return peers;
+}
+
 // Stable scatter of one radix pass.  Wave w ranks the contiguous quarter
-// [w SORT_TILE/4, (w+1) SORT_TILE/4) of the tile in 16 rounds of 64 records:
-// lanes holding the same digit are found with one ballot per digit bit, a
-// record's rank is the number of such lanes below it plus the wave's running
-// count of that digit (kept in LDS by the digit's lowest lane).  The tile's
-// order within a digit is therefore wave, round, lane: index order.  The tile
-// is ordered in LDS, then written so that each digit's run is contiguous in
-// memory.  Tiles are renumbered per XCD as in the histogram: a digit's runs
-// from neighbouring tiles are adjacent in the output, so their partial-line
-// stores meet in one L2.
+// [w TILE/4, (w+1) TILE/4) of the tile in IPT rounds of 64 records: a
+// record's rank is the number of lanes below it holding the same digit plus
+// the wave's running count of that digit (kept in LDS by the digit's lowest
+// lane).  The tile's order within a digit is therefore wave, round, lane: index
+// order.  The tile is ordered in LDS, keys first and then, through the same
+// buffer, record numbers, so that each digit's run is contiguous in memory.
+// Tiles are renumbered per XCD as in the histogram: a digit's runs from
+// neighbouring tiles are adjacent in the output, so their partial-line stores
+// meet in one L2.  The places past R in the last tile hold the largest key, so
+// they rank last and need no test until the stores.
+//
+// Bound by vector issue, not by its 16 bytes a record: 139 vector instructions
+// a round and 45 KB of LDS (3 workgroups a CU) with the ballots combined by
+// selects, bounds tests on every load and separate buffers for keys and
+// record numbers.
 //
 // SMALL: hoff holds the tiles' digit counts (tile-major) instead of their
 // scanned offsets, and the workgroup adds them up itself: every thread reads
 // its digits' column of the table, one row of B counts per tile.  That takes
 // the place of the two launches of the scan.
-template <int D, bool SMALL>
+template <int D, bool SMALL, int IPT>
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
     const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in,
     uint32_t* __restrict__ keys_out, uint32_t* __restrict__ vals_out, int64_t R, int shift,
     const uint32_t* __restrict__ hoff, int64_t tiles, const uint32_t* __restrict__ skip) {
     constexpr int B = 1 << D;
     constexpr int DPT = B / SORT_THREADS;  // digits per thread in the digit phase
-    constexpr int QUARTER = SORT_TILE / 4;
-    __shared__ uint32_t skeys[SORT_TILE];
-    __shared__ uint32_t svals[SORT_TILE];
-    __shared__ uint32_t wcnt[4][B];  // running counts, then exclusive prefixes over waves
-    __shared__ uint32_t dstart[B], goff[B];
+    constexpr int TILE = SORT_THREADS * IPT;
+    constexpr int QUARTER = TILE / 4;
+    __shared__ uint32_t buf[TILE];
+    // running counts of each wave, then where its records of a digit start in
+    // the tile (both at most TILE)
+    __shared__ uint16_t wcnt[4][B];
+    __shared__ uint32_t gdiff[B];  // a digit's place in the output less its place in the tile
     __shared__ uint32_t wsum[4];
     if (sort_skipped(skip)) return;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int64_t tile = xcd_block_id(blockIdx.x, gridDim.x);
-    const int64_t base = tile * SORT_TILE;
-    for (int d = t; d < B; d += SORT_THREADS) {
-        wcnt[0][d] = wcnt[1][d] = wcnt[2][d] = wcnt[3][d] = 0;
-        if constexpr (!SMALL) goff[d] = hoff[(int64_t)d * tiles + tile];
-    }
-    uint32_t k[SORT_IPT], v[SORT_IPT], loc[SORT_IPT];
-    const int64_t wbase = base + w * QUARTER;
+    const int64_t base = tile * TILE;
+    for (int d = t; d < 2 * B; d += SORT_THREADS) ((uint32_t*)wcnt)[d] = 0;
+    uint32_t k[IPT], v[IPT], loc[IPT];
+    const int64_t wbase = base + w * QUARTER + lane;
 #pragma unroll
-    for (int r = 0; r < SORT_IPT; r++) {
-        const int64_t i = wbase + r * 64 + lane;
-        k[r] = 0u;
-        v[r] = 0u;
-        if (i < R) {
-            k[r] = keys_in[i];
-            v[r] = vals_in ? vals_in[i] : (uint32_t)i;
-        }
+    for (int r = 0; r < IPT; r++) {
+        const int64_t i = wbase + r * 64;
+        const uint32_t q = keys_in[i < R ? i : R - 1];
+        k[r] = i < R ? q : ~0u;
     }
+    if (vals_in) {
+#pragma unroll
+        for (int r = 0; r < IPT; r++) {
+            const int64_t i = wbase + r * 64;
+            v[r] = vals_in[i < R ? i : R - 1];
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < IPT; r++) v[r] = (uint32_t)(wbase + r * 64);
+    }
+    uint32_t off[DPT];  // where the tile's records of thread t's digits t DPT .. go
     if constexpr (SMALL) {
-        // thread t's digits t DPT ..: their counts in the tiles before this
-        // one, and in all
+        // their counts in the tiles before this one, and in all
         uint32_t before[DPT], all[DPT], mine = 0;
 #pragma unroll
         for (int j = 0; j < DPT; j++) before[j] = all[j] = 0;
@@ -815,74 +842,70 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_scatter(
         uint32_t start = block_exclusive(mine, wsum, nullptr);
 #pragma unroll
         for (int j = 0; j < DPT; j++) {
-            goff[t * DPT + j] = start + before[j];
+            off[j] = start + before[j];
             start += all[j];
         }
+    } else {
+#pragma unroll
+        for (int j = 0; j < DPT; j++) off[j] = hoff[(int64_t)(t * DPT + j) * tiles + tile];
     }
     __syncthreads();
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
-    for (int r = 0; r < SORT_IPT; r++) {
-        const int64_t i = wbase + r * 64 + lane;
-        const bool valid = i < R;
+    for (int r = 0; r < IPT; r++) {
         const uint32_t dg = (k[r] >> shift) & (B - 1);
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int bit = 0; bit < D; bit++) {
-            const bool on = (dg >> bit) & 1u;
-            const uint64_t m = __ballot(on);
-            peers &= on ? m : ~m;
-        }
-        const uint32_t rank = (uint32_t)__popcll(peers & lt_mask);
-        const uint32_t before = valid ? wcnt[w][dg] : 0u;
+        const uint2 peers = digit_peers<D>(k[r], shift);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(peers.y, __builtin_amdgcn_mbcnt_lo(peers.x, 0u));
+        const uint32_t count = (uint32_t)(__popc(peers.x) + __popc(peers.y));
+        const uint32_t before = wcnt[w][dg];
         loc[r] = before + rank;
         wave_lds_sync();
-        if (valid && rank == 0) wcnt[w][dg] = before + (uint32_t)__popcll(peers);
+        if (rank == 0) wcnt[w][dg] = (uint16_t)(before + count);
         wave_lds_sync();
     }
     __syncthreads();
-    // digits: prefixes over the waves, and the tile's exclusive scan over digits
-    uint32_t tot[DPT], mine = 0;
+    // digits: the tile's exclusive scan over digits, and prefixes over the waves
+    uint32_t c[DPT][4], mine = 0;
 #pragma unroll
     for (int j = 0; j < DPT; j++) {
-        const int d = t * DPT + j;
-        const uint32_t c0 = wcnt[0][d], c1 = wcnt[1][d], c2 = wcnt[2][d], c3 = wcnt[3][d];
-        wcnt[0][d] = 0;
-        wcnt[1][d] = c0;
-        wcnt[2][d] = c0 + c1;
-        wcnt[3][d] = c0 + c1 + c2;
-        tot[j] = c0 + c1 + c2 + c3;
-        mine += tot[j];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            c[j][q] = wcnt[q][t * DPT + j];
+            mine += c[j][q];
+        }
     }
     uint32_t run = block_exclusive(mine, wsum, nullptr);
 #pragma unroll
     for (int j = 0; j < DPT; j++) {
-        dstart[t * DPT + j] = run;
-        run += tot[j];
-    }
-    __syncthreads();
+        gdiff[t * DPT + j] = off[j] - run;
 #pragma unroll
-    for (int r = 0; r < SORT_IPT; r++) {
-        const int64_t i = wbase + r * 64 + lane;
-        if (i < R) {
-            const uint32_t dg = (k[r] >> shift) & (B - 1);
-            const uint32_t pos = dstart[dg] + wcnt[w][dg] + loc[r];
-            skeys[pos] = k[r];
-            svals[pos] = v[r];
+        for (int q = 0; q < 4; q++) {
+            wcnt[q][t * DPT + j] = (uint16_t)run;
+            run += c[j][q];
         }
     }
     __syncthreads();
-    const int64_t nvalid = (R - base) < SORT_TILE ? (R - base) : SORT_TILE;
 #pragma unroll
-    for (int r = 0; r < SORT_IPT; r++) {
+    for (int r = 0; r < IPT; r++) {
+        loc[r] += wcnt[w][(k[r] >> shift) & (B - 1)];
+        buf[loc[r]] = k[r];
+    }
+    __syncthreads();
+    const int nvalid = (int)((R - base) < TILE ? (R - base) : TILE);
+#pragma unroll
+    for (int r = 0; r < IPT; r++) {
         const int p = r * SORT_THREADS + t;
-        if (p < nvalid) {
-            const uint32_t kk = skeys[p];
-            const uint32_t dg = (kk >> shift) & (B - 1);
-            const uint32_t dst = goff[dg] + ((uint32_t)p - dstart[dg]);
-            keys_out[dst] = kk;
-            vals_out[dst] = svals[p];
-        }
+        const uint32_t kk = buf[p];
+        k[r] = gdiff[(kk >> shift) & (B - 1)] + (uint32_t)p;  // from here on the destination
+        if (p < nvalid) keys_out[k[r]] = kk;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < IPT; r++) buf[loc[r]] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < IPT; r++) {
+        const int p = r * SORT_THREADS + t;
+        if (p < nvalid) vals_out[k[r]] = buf[p];
     }
 }
 
@@ -1664,8 +1687,24 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
         at += bits;
         widest = std::max(widest, bits);
     }
+    // A small sort is bound by its launches, so it makes fewer (its scatters add
+    // the tiles' digit counts up themselves, see launch_sort_records), at the
+    // price of a read of the whole table of counts by every workgroup.  A whole
+    // backward of 200,000 records took 104 us with the scans and 77 without (49
+    // tiles, 2^8 digits), 600,000 the same either way (147 tiles, 2^8 digits),
+    // 1,000,000 343 and 398 us (245 tiles, 2^10 digits).
     p->bins = 1 << std::max(8, widest);
-    p->tiles = (R + SORT_TILE - 1) / SORT_TILE;
+    const auto tiles_of = [&](int ipt) { return (R + SORT_THREADS * ipt - 1) / (SORT_THREADS * ipt); };
+    p->sort_ipt = SORT_IPT;
+    p->small_sort = tiles_of(SORT_IPT) * p->bins <= SMALL_SORT_COUNTS;
+    // Its few tiles leave most of the chip idle, and the rounds of a tile run one
+    // after the other: fewer keys per thread while the table stays below half
+    // that size (65,536 records and 2^9 digits: 46.8 us with 16, 44.7 with 8, 40.1
+    // with 4 keys; 50,001 and 2^10, past it: 45.7 with 8, 50.0 with 4).
+    while (p->small_sort && p->sort_ipt > 4 &&
+           tiles_of(p->sort_ipt / 2) * p->bins <= SMALL_SORT_COUNTS / 2)
+        p->sort_ipt /= 2;
+    p->tiles = tiles_of(p->sort_ipt);
     p->scan_len = (int64_t)p->bins * p->tiles;
     p->scan_blocks = (p->scan_len + SCAN_TILE - 1) / SCAN_TILE;
     p->chunks = (R + PIECE - 1) / PIECE;
@@ -1843,6 +1882,49 @@ hipError_t launch_backward(const TexView& t, int fmt, int mode, const float* uv,
     return launch_accumulate(t.n, t.C, mode, grad_out, out, plan, ws, clear.quads > 0, s);
 }
 
+template <bool SMALL, int IPT>
+static void launch_radix_hist(int D, const BwdPlan& plan, hipStream_t s, const uint32_t* kin,
+                              int shift, uint32_t* hist, const uint32_t* disorder) {
+    const dim3 grid((uint32_t)plan.tiles), block(SORT_THREADS);
+    prof_begin(K_RADIX_HIST, s);
+    if (D == 8) hipLaunchKernelGGL((k_radix_hist<8, SMALL, IPT>), grid, block, 0, s, kin, plan.records, shift, hist, plan.tiles, disorder);
+    else if (D == 9) hipLaunchKernelGGL((k_radix_hist<9, SMALL, IPT>), grid, block, 0, s, kin, plan.records, shift, hist, plan.tiles, disorder);
+    else hipLaunchKernelGGL((k_radix_hist<10, SMALL, IPT>), grid, block, 0, s, kin, plan.records, shift, hist, plan.tiles, disorder);
+    prof_end(K_RADIX_HIST, s);
+}
+
+template <bool SMALL, int IPT>
+static void launch_radix_scatter(int D, const BwdPlan& plan, hipStream_t s, const uint32_t* kin,
+                                 const uint32_t* vin, uint32_t* kout, uint32_t* vout, int shift,
+                                 const uint32_t* hoff, const uint32_t* disorder) {
+    const dim3 grid((uint32_t)plan.tiles), block(SORT_THREADS);
+    prof_begin(K_RADIX_SCATTER, s);
+    if (D == 8) hipLaunchKernelGGL((k_radix_scatter<8, SMALL, IPT>), grid, block, 0, s, kin, vin, kout, vout, plan.records, shift, hoff, plan.tiles, disorder);
+    else if (D == 9) hipLaunchKernelGGL((k_radix_scatter<9, SMALL, IPT>), grid, block, 0, s, kin, vin, kout, vout, plan.records, shift, hoff, plan.tiles, disorder);
+    else hipLaunchKernelGGL((k_radix_scatter<10, SMALL, IPT>), grid, block, 0, s, kin, vin, kout, vout, plan.records, shift, hoff, plan.tiles, disorder);
+    prof_end(K_RADIX_SCATTER, s);
+}
+
+// One pass of a small sort (the first one's digits are counted by the order
+// check, which is launched in place of the counting).
+template <int IPT>
+static void launch_small_pass(int pass, int D, const BwdPlan& plan, hipStream_t s,
+                              const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
+                              uint32_t* vout, uint32_t* hist, uint32_t* disorder, int2* range) {
+    if (pass == 0) {
+        const dim3 grid((uint32_t)plan.tiles), block(SORT_THREADS);
+        prof_begin(K_ORDER_CHECK, s);
+        if (D == 8) hipLaunchKernelGGL((k_keys_in_order_hist<8, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist);
+        else if (D == 9) hipLaunchKernelGGL((k_keys_in_order_hist<9, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist);
+        else hipLaunchKernelGGL((k_keys_in_order_hist<10, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist);
+        prof_end(K_ORDER_CHECK, s);
+    } else {
+        launch_radix_hist<true, IPT>(D, plan, s, kin, plan.digit_shift[pass], hist, disorder);
+    }
+    launch_radix_scatter<true, IPT>(D, plan, s, kin, vin, kout, vout, plan.digit_shift[pass], hist,
+                                    disorder);
+}
+
 // Whether the R keys in keys0 are in order, and their stable sort (record
 // numbers implied by position) if they are not: the order check leaves 0 or 1
 // in the workspace's disorder word (cleared before, returned), and with 0
@@ -1850,11 +1932,9 @@ hipError_t launch_backward(const TexView& t, int fmt, int mode, const float* uv,
 // the check also writes the bucket ranges the keys give if they are in order.
 // The sorted keys and their record numbers end in *skeys, *svals.
 //
-// A sort of up to SMALL_SORT_TILES tiles is bound by its launches, so it makes
-// fewer: its order check counts the first pass's digits, and its scatters add
-// the counts up themselves (2 launches a pass, 1 for the first, instead of 4).
-// That costs every workgroup a read of the whole table of counts, which grows
-// as the square of the tiles over the launch.
+// A small sort (see plan_backward) makes fewer launches: its order check counts
+// the first pass's digits, and its scatters add the counts up themselves (2
+// launches a pass, 1 for the first, instead of 4).
 static const uint32_t* launch_sort_records(const BwdPlan& plan, void* ws, int2* range,
                                            hipStream_t s, const uint32_t** skeys_out,
                                            const uint32_t** svals_out) {
@@ -1868,52 +1948,32 @@ static const uint32_t* launch_sort_records(const BwdPlan& plan, void* ws, int2* 
     uint32_t* scanp = (uint32_t*)(wsb + plan.off_scanp);
     uint32_t* disorder = (uint32_t*)(wsb + plan.off_disorder);
     const int64_t R = plan.records;
-    const bool small = plan.tiles <= SMALL_SORT_TILES;
-    const dim3 grid((uint32_t)plan.tiles), block(SORT_THREADS);
+    const bool small = plan.small_sort;
     const uint32_t* kin = keys0;
     const uint32_t* vin = nullptr;
-    prof_begin(K_ORDER_CHECK, s);
-    if (small) {
-        const int D = std::max(8, plan.digit_bits[0]);
-        if (D == 8) hipLaunchKernelGGL(k_keys_in_order_hist<8>, grid, block, 0, s, keys0, R, disorder, plan.cell_bits, plan.buckets, range, hist);
-        else if (D == 9) hipLaunchKernelGGL(k_keys_in_order_hist<9>, grid, block, 0, s, keys0, R, disorder, plan.cell_bits, plan.buckets, range, hist);
-        else hipLaunchKernelGGL(k_keys_in_order_hist<10>, grid, block, 0, s, keys0, R, disorder, plan.cell_bits, plan.buckets, range, hist);
-    } else {
-        hipLaunchKernelGGL(k_keys_in_order, dim3((uint32_t)((R + 1023) / 1024)), block, 0, s,
+    if (!small) {
+        prof_begin(K_ORDER_CHECK, s);
+        hipLaunchKernelGGL(k_keys_in_order, dim3((uint32_t)((R + 1023) / 1024)), dim3(256), 0, s,
                            keys0, R, disorder, plan.cell_bits, plan.buckets, range);
+        prof_end(K_ORDER_CHECK, s);
     }
-    prof_end(K_ORDER_CHECK, s);
     for (int pass = 0; pass < plan.passes; pass++) {
         uint32_t* kout = (pass & 1) ? keys0 : keys1;
         uint32_t* vout = (pass & 1) ? vals0 : vals1;
         const int shift = plan.digit_shift[pass];
         const int D = std::max(8, plan.digit_bits[pass]);
-        if (small) {
-            if (pass > 0) {
-                prof_begin(K_RADIX_HIST, s);
-                if (D == 8) hipLaunchKernelGGL((k_radix_hist<8, true>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-                else if (D == 9) hipLaunchKernelGGL((k_radix_hist<9, true>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-                else hipLaunchKernelGGL((k_radix_hist<10, true>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-                prof_end(K_RADIX_HIST, s);
-            }
-            prof_begin(K_RADIX_SCATTER, s);
-            if (D == 8) hipLaunchKernelGGL((k_radix_scatter<8, true>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hist, plan.tiles, disorder);
-            else if (D == 9) hipLaunchKernelGGL((k_radix_scatter<9, true>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hist, plan.tiles, disorder);
-            else hipLaunchKernelGGL((k_radix_scatter<10, true>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hist, plan.tiles, disorder);
-            prof_end(K_RADIX_SCATTER, s);
+        if (small && plan.sort_ipt == 4) {
+            launch_small_pass<4>(pass, D, plan, s, kin, vin, kout, vout, hist, disorder, range);
+        } else if (small && plan.sort_ipt == 8) {
+            launch_small_pass<8>(pass, D, plan, s, kin, vin, kout, vout, hist, disorder, range);
+        } else if (small) {
+            launch_small_pass<16>(pass, D, plan, s, kin, vin, kout, vout, hist, disorder, range);
         } else {
             const int64_t len = ((int64_t)1 << D) * plan.tiles;
-            prof_begin(K_RADIX_HIST, s);
-            if (D == 8) hipLaunchKernelGGL((k_radix_hist<8, false>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-            else if (D == 9) hipLaunchKernelGGL((k_radix_hist<9, false>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-            else hipLaunchKernelGGL((k_radix_hist<10, false>), grid, block, 0, s, kin, R, shift, hist, plan.tiles, disorder);
-            prof_end(K_RADIX_HIST, s);
+            launch_radix_hist<false, SORT_IPT>(D, plan, s, kin, shift, hist, disorder);
             launch_scan(hist, hoff, scanp, len, (len + SCAN_TILE - 1) / SCAN_TILE, s, disorder);
-            prof_begin(K_RADIX_SCATTER, s);
-            if (D == 8) hipLaunchKernelGGL((k_radix_scatter<8, false>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
-            else if (D == 9) hipLaunchKernelGGL((k_radix_scatter<9, false>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
-            else hipLaunchKernelGGL((k_radix_scatter<10, false>), grid, block, 0, s, kin, vin, kout, vout, R, shift, hoff, plan.tiles, disorder);
-            prof_end(K_RADIX_SCATTER, s);
+            launch_radix_scatter<false, SORT_IPT>(D, plan, s, kin, vin, kout, vout, shift, hoff,
+                                                  disorder);
         }
         kin = kout;
         vin = vout;

@@ -121,7 +121,9 @@ struct BwdPlan {
     int digit_bits[4];    // bits of each pass's digit (balanced)
     int digit_shift[4];   // position of each pass's digit in the key
     int bins;             // 2^D of the widest pass's kernel (D = 8, 9 or 10)
-    int64_t tiles;        // radix tiles
+    bool small_sort;      // the sort adds its tiles' digit counts up without a scan
+    int sort_ipt;         // keys per thread of a radix tile: 16, or 8 or 4 in a small sort
+    int64_t tiles;        // radix tiles of 256 sort_ipt keys
     int64_t scan_len;     // bins * tiles
     int64_t scan_blocks;  // partial sums of the scan
     int64_t chunks;       // fixed chunks of the sorted records (hot buckets)
@@ -144,7 +146,7 @@ constexpr int BIG_LISTS = 64; // big-bucket lists, each with its own counter
 constexpr int BIG_STRIDE = 64;  // u32 between two counters (256 bytes)
 constexpr int HOT_FLAG = 1;     // u32 after counter 0: set when a bucket needs pass 2
 constexpr int PAYLOAD_PER_THREAD = 4;  // sorted records per thread in the payload launch
-constexpr int SMALL_SORT_TILES = 64;  // sorts of up to this many tiles make fewer launches
+constexpr int64_t SMALL_SORT_COUNTS = 65536;  // digit counts (tiles x bins) of a small sort
 constexpr int BIG_RUN = 64;     // consecutive groups that append to one list
 // sparse: fragments whose upstream gradient is all zero make no records (their
 // keys sort past every bucket and are skipped), at the price of one key bit.
