@@ -194,9 +194,8 @@ hipError_t launch_vq_assign(const float* x, int64_t M, int D, const float* codeb
 //      counts laid out entry-major, hist[k][chunk];
 //   2. exclusive scan of hist: where each (entry, chunk) run starts in the
 //      rows sorted by entry;
-//   3. stable scatter of the row ids, chunk by chunk in rounds of 256 rows
-//      (a row's rank among the round's rows of its entry is counted from
-//      LDS), so each entry's rows end up in increasing order;
+//   3. stable scatter of the row ids, chunk by chunk (ranks from wave ballots),
+//      so each entry's rows end up in increasing order;
 //   4. each entry's rows are cut into pieces of VQ_PIECE; one workgroup sums a
 //      piece's rows in order; then one workgroup per entry sums its pieces in
 //      order and divides by the count (an entry with no row keeps its value).
@@ -221,46 +220,105 @@ __global__ __launch_bounds__(256) void k_vq_hist(const int32_t* __restrict__ ass
     for (int k = threadIdx.x; k < K; k += 256) hist[(int64_t)k * chunks + c] = cnt[k];
 }
 
+// Wave w ranks the contiguous quarter of its chunk in rounds of 64 rows: the
+// lanes holding the same entry are found with one ballot per bit of the entry
+// number, a row's place among the chunk's rows of its entry is the wave's
+// running count (in LDS, advanced by the entry's lowest lane) plus the number of
+// such lanes below it, and the waves' counts are added up at the end.  262,144
+// rows of 256 entries: 124 -> 18 us against comparing every row of a round with
+// the 255 others.
+template <int BITS>
 __global__ __launch_bounds__(256) void k_vq_scatter(const int32_t* __restrict__ assign, int64_t M,
                                                     int K, int64_t chunks,
                                                     const uint32_t* __restrict__ offs,
                                                     uint32_t* __restrict__ sorted) {
-    __shared__ uint32_t base[VQ_MAX_UPDATE_ENTRIES];
-    __shared__ int keys[256];
+    constexpr int ROUNDS = VQ_CHUNK / 256;
+    __shared__ uint16_t cnt[4][1 << BITS];  // at most VQ_CHUNK / 4 rows a wave
     const int64_t c = blockIdx.x;
-    for (int k = threadIdx.x; k < K; k += 256) base[k] = offs[(int64_t)k * chunks + c];
-    const int64_t r0 = c * VQ_CHUNK;
-    const int64_t r1 = std::min<int64_t>(r0 + VQ_CHUNK, M);
-    for (int64_t rb = r0; rb < r1; rb += 256) {
-        const int64_t r = rb + threadIdx.x;
-        const int k = r < r1 ? vq_entry(assign, r, K) : -1;
-        __syncthreads();  // base is current, keys free
-        keys[threadIdx.x] = k;
-        __syncthreads();
-        int rank = 0, after = 0;
-        if (k >= 0) {
-            for (int q = 0; q < 256; q++) {
-                const int kq = keys[q];
-                rank += (q < (int)threadIdx.x && kq == k) ? 1 : 0;
-                after += (q > (int)threadIdx.x && kq == k) ? 1 : 0;
-            }
-            sorted[base[k] + rank] = (uint32_t)r;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (int k = threadIdx.x; k < (4 << BITS) / 2; k += 256) ((uint32_t*)cnt)[k] = 0;
+    const int64_t r0 = c * VQ_CHUNK + w * (VQ_CHUNK / 4) + lane;
+    int e[ROUNDS];
+    uint32_t place[ROUNDS];
+#pragma unroll
+    for (int q = 0; q < ROUNDS; q++) {
+        const int64_t r = r0 + q * 64;
+        e[q] = vq_entry(assign, r < M ? r : M - 1, K);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < ROUNDS; q++) {
+        uint64_t peers = __ballot(r0 + q * 64 < M);
+#pragma unroll
+        for (int bit = 0; bit < BITS; bit++) {
+            const bool on = (e[q] >> bit) & 1;
+            const uint64_t m = __ballot(on);
+            peers &= on ? m : ~m;
         }
-        __syncthreads();  // every thread has read base
-        if (k >= 0 && after == 0) base[k] += (uint32_t)(rank + 1);
+        const bool live = r0 + q * 64 < M;
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+        const uint32_t before = cnt[w][e[q]];
+        place[q] = before + rank;
+        wave_lds_sync();
+        if (live && rank == 0) cnt[w][e[q]] = (uint16_t)(before + __popcll(peers));
+        wave_lds_sync();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < ROUNDS; q++) {
+        const int64_t r = r0 + q * 64;
+        if (r < M) {
+            uint32_t at = offs[(int64_t)e[q] * chunks + c] + place[q];
+            for (int v = 0; v < w; v++) at += cnt[v][e[q]];
+            sorted[at] = (uint32_t)r;
+        }
     }
 }
 
-// pieces of each entry: ptab[k] = ceil(count_k / VQ_PIECE); count_k from the
-// scanned offsets (the scan's value past the last element is the total M)
+// pieces of each entry, ptab[k] = ceil(count_k / VQ_PIECE) with count_k from the
+// scanned offsets (the scan's value past the last element is the total M), and
+// their exclusive scan pstart, by one workgroup: thread t owns PER consecutive
+// entries
 __global__ __launch_bounds__(256) void k_vq_piece_table(const uint32_t* __restrict__ offs, int K,
                                                         int64_t chunks, int64_t M,
-                                                        uint32_t* __restrict__ ptab) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= K) return;
-    const uint32_t start = offs[(int64_t)k * chunks];
-    const uint32_t end = k + 1 < K ? offs[(int64_t)(k + 1) * chunks] : (uint32_t)M;
-    ptab[k] = (end - start + VQ_PIECE - 1) / VQ_PIECE;
+                                                        uint32_t* __restrict__ ptab,
+                                                        uint32_t* __restrict__ pstart) {
+    constexpr int PER = VQ_MAX_UPDATE_ENTRIES / 256;
+    __shared__ uint32_t wsum[4];
+    const int per = (K + 255) / 256, k0 = threadIdx.x * per;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t n[PER], mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER; j++) {
+        const int k = k0 + j;
+        n[j] = 0;
+        if (j < per && k < K) {
+            const uint32_t start = offs[(int64_t)k * chunks];
+            const uint32_t end = k + 1 < K ? offs[(int64_t)(k + 1) * chunks] : (uint32_t)M;
+            n[j] = (end - start + VQ_PIECE - 1) / VQ_PIECE;
+        }
+        mine += n[j];
+    }
+    uint32_t x = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    uint32_t run = x - mine;
+    for (int v = 0; v < w; v++) run += wsum[v];
+#pragma unroll
+    for (int j = 0; j < PER; j++) {
+        const int k = k0 + j;
+        if (j < per && k < K) {
+            ptab[k] = n[j];
+            pstart[k] = run;
+        }
+        run += n[j];
+    }
 }
 
 // one workgroup per piece: sum its rows in order (columns over the threads)
@@ -355,7 +413,6 @@ bool plan_vq_update(int64_t M, int D, int K, VqPlan* p) {
     p->off_sorted = take((size_t)M * 4);
     p->off_ptab = take((size_t)K * 4);
     p->off_pstart = take((size_t)K * 4);
-    p->off_ppart = take((size_t)((K + 4095) / 4096 + 1) * 4);
     p->off_sums = take((size_t)p->pieces_max * D * 4);
     p->total = off;
     return true;
@@ -370,7 +427,6 @@ hipError_t launch_vq_update(const float* x, const int32_t* assign, float* codebo
     uint32_t* sorted = (uint32_t*)(base + p.off_sorted);
     uint32_t* ptab = (uint32_t*)(base + p.off_ptab);
     uint32_t* pstart = (uint32_t*)(base + p.off_pstart);
-    uint32_t* ppart = (uint32_t*)(base + p.off_ppart);
     float* psum = (float*)(base + p.off_sums);
     prof_begin(K_VQ_HIST, s);
     hipLaunchKernelGGL(k_vq_hist, dim3((uint32_t)p.chunks), dim3(256), 0, s, assign, p.M, p.K,
@@ -379,13 +435,13 @@ hipError_t launch_vq_update(const float* x, const int32_t* assign, float* codebo
     hipError_t e = launch_exclusive_scan(hist, offs, part, p.hist_len, s);
     if (e != hipSuccess) return e;
     prof_begin(K_VQ_SCATTER, s);
-    hipLaunchKernelGGL(k_vq_scatter, dim3((uint32_t)p.chunks), dim3(256), 0, s, assign, p.M, p.K,
-                       p.chunks, (const uint32_t*)offs, sorted);
-    hipLaunchKernelGGL(k_vq_piece_table, dim3((uint32_t)((p.K + 255) / 256)), dim3(256), 0, s,
-                       (const uint32_t*)offs, p.K, p.chunks, p.M, ptab);
+    const dim3 gc((uint32_t)p.chunks), block(256);
+    if (p.K <= 256) hipLaunchKernelGGL(k_vq_scatter<8>, gc, block, 0, s, assign, p.M, p.K, p.chunks, (const uint32_t*)offs, sorted);
+    else if (p.K <= 1024) hipLaunchKernelGGL(k_vq_scatter<10>, gc, block, 0, s, assign, p.M, p.K, p.chunks, (const uint32_t*)offs, sorted);
+    else hipLaunchKernelGGL(k_vq_scatter<12>, gc, block, 0, s, assign, p.M, p.K, p.chunks, (const uint32_t*)offs, sorted);
+    hipLaunchKernelGGL(k_vq_piece_table, dim3(1), block, 0, s, (const uint32_t*)offs, p.K,
+                       p.chunks, p.M, ptab, pstart);
     prof_end(K_VQ_SCATTER, s);
-    e = launch_exclusive_scan(ptab, pstart, ppart, p.K, s);
-    if (e != hipSuccess) return e;
     prof_begin(K_VQ_PIECES, s);
     hipLaunchKernelGGL(k_vq_piece_sum, dim3((uint32_t)p.pieces_max), dim3(256), 0, s, x, p.M, p.D,
                        p.K, p.chunks, (const uint32_t*)offs, (const uint32_t*)pstart,

@@ -207,8 +207,7 @@ struct VqPlan {
     int64_t M;
     int D, K;
     int64_t chunks, hist_len, pieces_max;
-    size_t off_hist, off_offs, off_part, off_sorted, off_ptab, off_pstart, off_ppart, off_sums,
-        total;
+    size_t off_hist, off_offs, off_part, off_sorted, off_ptab, off_pstart, off_sums, total;
 };
 bool plan_vq_update(int64_t M, int D, int K, VqPlan* p);
 hipError_t launch_vq_assign(const float* x, int64_t M, int D, const float* codebook, int K,
