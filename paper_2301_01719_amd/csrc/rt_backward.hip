@@ -85,11 +85,14 @@ __device__ __forceinline__ void bucket_grads(const TexView& t, int64_t b, const 
                                              const float go[4], float& dsx, float& dsy,
                                              float& lval) {
     const int n = t.n;
-    const int64_t base = b * (int64_t)(n * n);
-    F4 t00 = load_texel<FMT, C>(t.data, base + p.y0 * n + p.x0);
-    F4 t01 = load_texel<FMT, C>(t.data, base + p.y0 * n + p.x1);
-    F4 t10 = load_texel<FMT, C>(t.data, base + p.y1 * n + p.x0);
-    F4 t11 = load_texel<FMT, C>(t.data, base + p.y1 * n + p.x1);
+    using Row = RowBits<FMT, C>;
+    const unsigned char* src[1] = {(const unsigned char*)t.data +
+                                   (b * (int64_t)(n * n) + p.y0 * n + p.x0) * Row::TEXEL};
+    Row row[1][2];
+    load_rows<FMT, C, 1>(src, n, row);
+    F4 t00, t01, t10, t11;
+    row[0][0].decode(t00, t01);
+    row[0][1].decode(t10, t11);
     float f = bucket_factor<FMT>(t.scales, b);
     float gx = 0.f, gy = 0.f, lv = 0.f;
     float w00 = (1.f - p.fx) * (1.f - p.fy), w01 = p.fx * (1.f - p.fy);
@@ -119,16 +122,22 @@ __device__ __forceinline__ void pair_grads(const TexView& t, const int64_t bk[4]
                                            bool want_uv, float& gsx, float& gsy, float& gu,
                                            float& gv) {
     const int n = t.n;
+    using Row = RowBits<FMT, C>;
+    const unsigned char* src[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        src[k] = (const unsigned char*)t.data +
+                 (bk[k] * (int64_t)(n * n) + p.y0 * n + p.x0) * Row::TEXEL;
+    Row row[4][2];
+    load_rows<FMT, C, 4>(src, n, row);
     float T[4][4][4];  // [bucket][tap 00, 01, 10, 11][channel], times the bucket factor
     gsx = 0.f;
     gsy = 0.f;
 #pragma unroll
     for (int k = 0; k < 4; k++) {
-        const int64_t base = bk[k] * (int64_t)(n * n);
-        const F4 t00 = load_texel<FMT, C>(t.data, base + p.y0 * n + p.x0);
-        const F4 t01 = load_texel<FMT, C>(t.data, base + p.y0 * n + p.x1);
-        const F4 t10 = load_texel<FMT, C>(t.data, base + p.y1 * n + p.x0);
-        const F4 t11 = load_texel<FMT, C>(t.data, base + p.y1 * n + p.x1);
+        F4 t00, t01, t10, t11;
+        row[k][0].decode(t00, t01);
+        row[k][1].decode(t10, t11);
         const float f = bucket_factor<FMT>(t.scales, bk[k]);
         float gx = 0.f, gy = 0.f;
 #pragma unroll
@@ -244,6 +253,10 @@ __global__ __launch_bounds__(256) void k_bwd_fragment(
         int64_t b = (int64_t)j * t.W + i;
         float lv;
         if (grad_view) bucket_grads<FMT, C>(t, b, p, go, gsx, gsy, lv);
+        // no store before the taps have arrived: one counter tracks a
+        // wavefront's loads and stores in order, so a wait for loads issued
+        // after stores waits for those too
+        __builtin_amdgcn_sched_barrier(0);
         if (grad_uv) nt_store2(grad_uv + 2 * f, 0.f, 0.f);
         if (keys) {
             __builtin_nontemporal_store(((uint32_t)b << cell_bits) | cell, keys + f);
@@ -260,6 +273,7 @@ __global__ __launch_bounds__(256) void k_bwd_fragment(
         if (grad_view || grad_uv) {
             float gu, gv;
             pair_grads<FMT, C>(t, bk, wb, a, bb, p, go, grad_uv != nullptr, gsx, gsy, gu, gv);
+            __builtin_amdgcn_sched_barrier(0);  // as above
             if (grad_uv) nt_store2(grad_uv + 2 * f, gu, gv);
         }
         if (keys) {

@@ -16,52 +16,104 @@
 
 namespace rt {
 
-// The four taps around footprint p of the bucket whose first texel is at
-// `bucket` (global memory or a copy in LDS), blended and added to acc with
-// factor f.
-template <int FMT, int C>
-__device__ __forceinline__ void blend_taps(const void* bucket, int n, const Foot& p, float f,
-                                           float acc[4]) {
-    F4 t00 = load_texel<FMT, C>(bucket, p.y0 * n + p.x0);
-    F4 t01 = load_texel<FMT, C>(bucket, p.y0 * n + p.x1);
-    F4 t10 = load_texel<FMT, C>(bucket, p.y1 * n + p.x0);
-    F4 t11 = load_texel<FMT, C>(bucket, p.y1 * n + p.x1);
-    float w00 = (1.f - p.fx) * (1.f - p.fy), w01 = p.fx * (1.f - p.fy);
-    float w10 = (1.f - p.fx) * p.fy, w11 = p.fx * p.fy;
+// Four taps blended and added to acc with factor f, in operations that leave
+// the compiler no choice of which products to fuse: every kernel that blends
+// gives the same bits.
+template <int C>
+__device__ __forceinline__ void blend(const F4& t00, const F4& t01, const F4& t10, const F4& t11,
+                                      const Foot& p, float f, float acc[4]) {
+    const float w00 = (1.f - p.fx) * (1.f - p.fy), w01 = p.fx * (1.f - p.fy);
+    const float w10 = (1.f - p.fx) * p.fy, w11 = p.fx * p.fy;
 #pragma unroll
     for (int c = 0; c < C; c++) {
-        float v = w00 * t00.v[c] + w01 * t01.v[c] + w10 * t10.v[c] + w11 * t11.v[c];
-        acc[c] += f * v;
+        const float v = fmaf(w11, t11.v[c], fmaf(w10, t10.v[c], fmaf(w01, t01.v[c], w00 * t00.v[c])));
+        acc[c] = fmaf(f, v, acc[c]);
     }
 }
 
-// The four taps of bucket b around footprint p, blended and added to acc
-// with weight wgt.  DICT: b is read through the dictionary (its entry in the
-// codebook, times its gain).
-template <int FMT, int C, bool DICT = false>
-__device__ __forceinline__ void bucket_bilerp(const TexView& t, int64_t b, const Foot& p,
-                                              float wgt, float acc[4]) {
+// The four taps around footprint p of the bucket whose first texel is at
+// `bucket` in LDS, blended and added to acc with factor f.
+template <int FMT, int C>
+__device__ __forceinline__ void blend_staged(const void* bucket, int n, const Foot& p, float f,
+                                             float acc[4]) {
+    blend<C>(load_texel<FMT, C>(bucket, p.y0 * n + p.x0), load_texel<FMT, C>(bucket, p.y0 * n + p.x1),
+             load_texel<FMT, C>(bucket, p.y1 * n + p.x0), load_texel<FMT, C>(bucket, p.y1 * n + p.x1),
+             p, f, acc);
+}
+
+// The taps of NB buckets bk around footprint p, blended bucket by bucket and
+// added to acc with weights wgt.  DICT: a bucket is read through the dictionary
+// (its entry in the codebook, times its gain).
+template <int FMT, int C, int NB, bool DICT = false>
+__device__ __forceinline__ void buckets_bilerp(const TexView& t, const int64_t bk[NB],
+                                               const Foot& p, const float wgt[NB], float acc[4]) {
     const int n = t.n;
-    if constexpr (DICT) {
-        if (t.gains) wgt *= t.gains[b];
-        b = dict_entry(t, b);
+    float f[NB];
+    int64_t b[NB];
+#pragma unroll
+    for (int k = 0; k < NB; k++) {
+        b[k] = bk[k];
+        f[k] = wgt[k];
+        if constexpr (DICT) {
+            if (t.gains) f[k] *= t.gains[b[k]];
+            b[k] = dict_entry(t, b[k]);
+        }
     }
     if constexpr (FMT == FMT_BIT1) {
-        const uint32_t* w = (const uint32_t*)t.data + b * bit_words(n);
         const int k00 = p.y0 * n + p.x0, k01 = p.y0 * n + p.x1;
         const int k10 = p.y1 * n + p.x0, k11 = p.y1 * n + p.x1;
-        const float t00 = (float)((w[k00 >> 5] >> (k00 & 31)) & 1u);
-        const float t01 = (float)((w[k01 >> 5] >> (k01 & 31)) & 1u);
-        const float t10 = (float)((w[k10 >> 5] >> (k10 & 31)) & 1u);
-        const float t11 = (float)((w[k11 >> 5] >> (k11 & 31)) & 1u);
-        const float v = (1.f - p.fx) * (1.f - p.fy) * t00 + p.fx * (1.f - p.fy) * t01 +
-                        (1.f - p.fx) * p.fy * t10 + p.fx * p.fy * t11;
-        acc[0] += wgt * v;
-        return;
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            const uint32_t* w = (const uint32_t*)t.data + b[k] * bit_words(n);
+            const float t00 = (float)((w[k00 >> 5] >> (k00 & 31)) & 1u);
+            const float t01 = (float)((w[k01 >> 5] >> (k01 & 31)) & 1u);
+            const float t10 = (float)((w[k10 >> 5] >> (k10 & 31)) & 1u);
+            const float t11 = (float)((w[k11 >> 5] >> (k11 & 31)) & 1u);
+            const float v = (1.f - p.fx) * (1.f - p.fy) * t00 + p.fx * (1.f - p.fy) * t01 +
+                            (1.f - p.fx) * p.fy * t10 + p.fx * p.fy * t11;
+            acc[0] += f[k] * v;
+        }
+    } else {
+        using Row = RowBits<FMT, C>;
+        const unsigned char* src[NB];
+#pragma unroll
+        for (int k = 0; k < NB; k++)
+            src[k] = (const unsigned char*)t.data +
+                     (b[k] * (int64_t)(n * n) + p.y0 * n + p.x0) * Row::TEXEL;
+        Row row[NB][2];
+        load_rows<FMT, C, NB>(src, n, row);
+#pragma unroll
+        for (int k = 0; k < NB; k++) f[k] *= bucket_factor<FMT>(t.scales, b[k]);
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+            F4 t00, t01, t10, t11;
+            row[k][0].decode(t00, t01);
+            row[k][1].decode(t10, t11);
+            blend<C>(t00, t01, t10, t11, p, f[k], acc);
+        }
     }
-    const unsigned char* bucket =
-        (const unsigned char*)t.data + b * (int64_t)(n * n) * C * storage_bytes<FMT>();
-    blend_taps<FMT, C>(bucket, n, p, wgt * bucket_factor<FMT>(t.scales, b), acc);
+}
+
+// The lookup at footprint p in the matrix t: the bucket of (u, v), or the four
+// around it with their weights.
+template <int FMT, int C, int MODE, bool DICT = false>
+__device__ __forceinline__ void matrix_lookup(const TexView& t, float u, float v, const Foot& p,
+                                              float acc[4]) {
+    if constexpr (MODE == MODE_NEAREST) {
+        const int i = bucket_of(u, t.W), j = bucket_of(v, t.H);
+        const int64_t bk[1] = {(int64_t)j * t.W + i};
+        const float wgt[1] = {1.0f};
+        buckets_bilerp<FMT, C, 1, DICT>(t, bk, p, wgt, acc);
+    } else {
+        int i0, i1, j0, j1;
+        float a, bb;
+        bucket_pair(u, t.W, i0, i1, a);
+        bucket_pair(v, t.H, j0, j1, bb);
+        const int64_t bk[4] = {(int64_t)j0 * t.W + i0, (int64_t)j0 * t.W + i1,
+                               (int64_t)j1 * t.W + i0, (int64_t)j1 * t.W + i1};
+        const float wgt[4] = {(1.f - a) * (1.f - bb), a * (1.f - bb), (1.f - a) * bb, a * bb};
+        buckets_bilerp<FMT, C, 4, DICT>(t, bk, p, wgt, acc);
+    }
 }
 
 // The lookup's output is written once and not read back by the library: it
@@ -89,19 +141,7 @@ __global__ __launch_bounds__(256) void k_lookup_fwd(TexView t, const float* __re
     Dir d = map_direction(g.m, g.w, t.n);
     Foot p = footprint(d.sx, d.sy, t.n);
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (MODE == MODE_NEAREST) {
-        int i = bucket_of(g.u, t.W), j = bucket_of(g.v, t.H);
-        bucket_bilerp<FMT, C, DICT>(t, (int64_t)j * t.W + i, p, 1.0f, acc);
-    } else {
-        int i0, i1, j0, j1;
-        float a, bb;
-        bucket_pair(g.u, t.W, i0, i1, a);
-        bucket_pair(g.v, t.H, j0, j1, bb);
-        bucket_bilerp<FMT, C, DICT>(t, (int64_t)j0 * t.W + i0, p, (1.f - a) * (1.f - bb), acc);
-        bucket_bilerp<FMT, C, DICT>(t, (int64_t)j0 * t.W + i1, p, a * (1.f - bb), acc);
-        bucket_bilerp<FMT, C, DICT>(t, (int64_t)j1 * t.W + i0, p, (1.f - a) * bb, acc);
-        bucket_bilerp<FMT, C, DICT>(t, (int64_t)j1 * t.W + i1, p, a * bb, acc);
-    }
+    matrix_lookup<FMT, C, MODE, DICT>(t, g.u, g.v, p, acc);
     store_out<C>(out, f, acc);
 }
 
@@ -110,7 +150,7 @@ __global__ __launch_bounds__(256) void k_lookup_fwd(TexView t, const float* __re
 // is found with a ballot, every lane whose fragment lies in that bucket joins
 // the group, the wavefront copies the whole bucket into its LDS tile with
 // 16-byte loads, and the group blends its taps from LDS; repeated until every
-// fragment is served.  The blend is blend_taps on the copy, so the results
+// fragment is served.  The blend is the same on the copy, so the results
 // are those of k_lookup_fwd bit for bit.  It pays only where a wavefront's
 // fragments share few buckets and read much of each.
 template <int FMT, int C>
@@ -145,7 +185,7 @@ __global__ __launch_bounds__(256) void k_lookup_fwd_staged(TexView t, const floa
         for (int q = lane; q < bucket_bytes / 16; q += 64) mine[q] = src[q];
         wave_lds_sync();
         if ((grp >> lane) & 1ull)
-            blend_taps<FMT, C>(mine, t.n, p, 1.0f * bucket_factor<FMT>(t.scales, bk), acc);
+            blend_staged<FMT, C>(mine, t.n, p, 1.0f * bucket_factor<FMT>(t.scales, bk), acc);
         wave_lds_sync();
         todo &= ~grp;
     }
@@ -191,19 +231,7 @@ __device__ __forceinline__ void level_lookup(const LevelSet& ls, int l, const Fr
     t.H = max(ls.H >> l, 1);
     t.n = ls.n;
     t.C = ls.C;
-    if constexpr (MODE == MODE_NEAREST) {
-        const int i = bucket_of(g.u, t.W), j = bucket_of(g.v, t.H);
-        bucket_bilerp<FMT, C>(t, (int64_t)j * t.W + i, p, 1.0f, acc);
-    } else {
-        int i0, i1, j0, j1;
-        float a, bb;
-        bucket_pair(g.u, t.W, i0, i1, a);
-        bucket_pair(g.v, t.H, j0, j1, bb);
-        bucket_bilerp<FMT, C>(t, (int64_t)j0 * t.W + i0, p, (1.f - a) * (1.f - bb), acc);
-        bucket_bilerp<FMT, C>(t, (int64_t)j0 * t.W + i1, p, a * (1.f - bb), acc);
-        bucket_bilerp<FMT, C>(t, (int64_t)j1 * t.W + i0, p, (1.f - a) * bb, acc);
-        bucket_bilerp<FMT, C>(t, (int64_t)j1 * t.W + i1, p, a * bb, acc);
-    }
+    matrix_lookup<FMT, C, MODE>(t, g.u, g.v, p, acc);
 }
 
 // Lookup over a mip chain of bucket matrices: the level of detail is
@@ -483,8 +511,10 @@ __global__ __launch_bounds__(256) void k_lookup_light(TexView t, const float* __
         }
     }
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    // (four samples' vectors, scalar loads, are read at a time)
-#pragma unroll 4
+    // (four samples' vectors, scalar loads, are read at a time; not where a
+    // sample's taps are gathered, which would need twice the registers)
+    constexpr int AT_ONCE = CACHE ? 4 : 1;
+#pragma unroll AT_ONCE
     for (int s = 0; s < lp.samples; s++) {
         float L[3];
 #pragma unroll
@@ -531,9 +561,7 @@ __global__ __launch_bounds__(256) void k_lookup_light(TexView t, const float* __
                 }
             }
         } else {
-#pragma unroll
-            for (int r = 0; r < NB; r++)
-                bucket_bilerp<FMT, C, DICT>(t, bk[r], footprint(sx, sy, n), bw[r], acc);
+            buckets_bilerp<FMT, C, NB, DICT>(t, bk, footprint(sx, sy, n), bw, acc);
         }
     }
 #pragma unroll
