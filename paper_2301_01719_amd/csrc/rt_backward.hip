@@ -62,28 +62,43 @@ __device__ __forceinline__ void square_vjp(float ax, float ay, float gbx, float 
         gay = gby;
         return;
     }
-    if (fabsf(ax) >= fabsf(ay)) {
-        float sx = ax >= 0.f ? 1.f : -1.f;
-        float j00 = fabsf(ax) / rho, j01 = sx * ay / rho;
-        float j10 = -sx * ay * ay * ay / (rho * ax * ax);
-        float j11 = (ay * ay + rho * rho) / (rho * fabsf(ax));
-        gax = j00 * gbx + j10 * gby;
-        gay = j01 * gbx + j11 * gby;
-    } else {
-        float sy = ay >= 0.f ? 1.f : -1.f;
-        float j11 = fabsf(ay) / rho, j10 = sy * ax / rho;
-        float j01 = -sy * ax * ax * ax / (rho * ay * ay);
-        float j00 = (ax * ax + rho * rho) / (rho * fabsf(ay));
-        gax = j00 * gbx + j10 * gby;
-        gay = j01 * gbx + j11 * gby;
-    }
+    // the branches differ in the axes' names only: evaluated once, by the larger
+    // and the smaller axis (a wavefront has lanes on both)
+    const bool xl = fabsf(ax) >= fabsf(ay);
+    const float p = xl ? ax : ay, q = xl ? ay : ax;
+    const float gbp = xl ? gbx : gby, gbq = xl ? gby : gbx;
+    const float s = p >= 0.f ? 1.f : -1.f;
+    const float jpp = fabsf(p) / rho, jpq = s * q / rho;
+    const float jqp = -s * q * q * q / (rho * p * p);
+    const float jqq = (q * q + rho * rho) / (rho * fabsf(p));
+    const float gp = jpp * gbp + jqp * gbq, gq = jpq * gbp + jqq * gbq;
+    gax = xl ? gp : gq;
+    gay = xl ? gq : gp;
 }
 
-// Per-bucket part of the per-fragment backward: dL/ds (x, y) and sum_c g_c * value.
+// sum_c g_c times the slopes of the blended texels along x and y: the
+// differences of neighbouring taps are summed over the channels first, then
+// weighted (8 operations a channel).
+template <int C>
+__device__ __forceinline__ void tap_slopes(const F4& t00, const F4& t01, const F4& t10,
+                                           const F4& t11, const Foot& p, const float go[4],
+                                           float& gx, float& gy) {
+    float top = 0.f, bottom = 0.f, left = 0.f, right = 0.f;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        top += go[c] * (t01.v[c] - t00.v[c]);
+        bottom += go[c] * (t11.v[c] - t10.v[c]);
+        left += go[c] * (t10.v[c] - t00.v[c]);
+        right += go[c] * (t11.v[c] - t01.v[c]);
+    }
+    gx = (1.f - p.fy) * top + p.fy * bottom;
+    gy = (1.f - p.fx) * left + p.fx * right;
+}
+
+// Per-bucket part of the per-fragment backward: dL/ds (x, y).
 template <int FMT, int C>
 __device__ __forceinline__ void bucket_grads(const TexView& t, int64_t b, const Foot& p,
-                                             const float go[4], float& dsx, float& dsy,
-                                             float& lval) {
+                                             const float go[4], float& dsx, float& dsy) {
     const int n = t.n;
     using Row = RowBits<FMT, C>;
     const unsigned char* src[1] = {(const unsigned char*)t.data +
@@ -93,19 +108,11 @@ __device__ __forceinline__ void bucket_grads(const TexView& t, int64_t b, const 
     F4 t00, t01, t10, t11;
     row[0][0].decode(t00, t01);
     row[0][1].decode(t10, t11);
-    float f = bucket_factor<FMT>(t.scales, b);
-    float gx = 0.f, gy = 0.f, lv = 0.f;
-    float w00 = (1.f - p.fx) * (1.f - p.fy), w01 = p.fx * (1.f - p.fy);
-    float w10 = (1.f - p.fx) * p.fy, w11 = p.fx * p.fy;
-#pragma unroll
-    for (int c = 0; c < C; c++) {
-        gx += go[c] * ((1.f - p.fy) * (t01.v[c] - t00.v[c]) + p.fy * (t11.v[c] - t10.v[c]));
-        gy += go[c] * ((1.f - p.fx) * (t10.v[c] - t00.v[c]) + p.fx * (t11.v[c] - t01.v[c]));
-        lv += go[c] * (w00 * t00.v[c] + w01 * t01.v[c] + w10 * t10.v[c] + w11 * t11.v[c]);
-    }
+    const float f = bucket_factor<FMT>(t.scales, b);
+    float gx, gy;
+    tap_slopes<C>(t00, t01, t10, t11, p, go, gx, gy);
     dsx = f * gx;
     dsy = f * gy;
-    lval = f * lv;
 }
 
 // Bilinear-bucket mode: the slopes dL/ds of the four buckets (weighted by
@@ -139,11 +146,10 @@ __device__ __forceinline__ void pair_grads(const TexView& t, const int64_t bk[4]
         row[k][0].decode(t00, t01);
         row[k][1].decode(t10, t11);
         const float f = bucket_factor<FMT>(t.scales, bk[k]);
-        float gx = 0.f, gy = 0.f;
+        float gx, gy;
+        tap_slopes<C>(t00, t01, t10, t11, p, go, gx, gy);
 #pragma unroll
         for (int c = 0; c < C; c++) {
-            gx += go[c] * ((1.f - p.fy) * (t01.v[c] - t00.v[c]) + p.fy * (t11.v[c] - t10.v[c]));
-            gy += go[c] * ((1.f - p.fx) * (t10.v[c] - t00.v[c]) + p.fx * (t11.v[c] - t01.v[c]));
             T[k][0][c] = f * t00.v[c];
             T[k][1][c] = f * t01.v[c];
             T[k][2][c] = f * t10.v[c];
@@ -159,15 +165,17 @@ __device__ __forceinline__ void pair_grads(const TexView& t, const int64_t bk[4]
                         p.fx * p.fy};
     float su = 0.f, sv = 0.f;
 #pragma unroll
-    for (int c = 0; c < C; c++) {
-        float du = 0.f, dv = 0.f;
+    for (int q = 0; q < 4; q++) {
+        float top = 0.f, bottom = 0.f, left = 0.f, right = 0.f;
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            du += w[q] * ((1.f - bb) * (T[1][q][c] - T[0][q][c]) + bb * (T[3][q][c] - T[2][q][c]));
-            dv += w[q] * ((1.f - a) * (T[2][q][c] - T[0][q][c]) + a * (T[3][q][c] - T[1][q][c]));
+        for (int c = 0; c < C; c++) {
+            top += go[c] * (T[1][q][c] - T[0][q][c]);
+            bottom += go[c] * (T[3][q][c] - T[2][q][c]);
+            left += go[c] * (T[2][q][c] - T[0][q][c]);
+            right += go[c] * (T[3][q][c] - T[1][q][c]);
         }
-        su += go[c] * du;
-        sv += go[c] * dv;
+        su += w[q] * ((1.f - bb) * top + bb * bottom);
+        sv += w[q] * ((1.f - a) * left + a * right);
     }
     gu = (float)t.W * su;
     gv = (float)t.H * sv;
@@ -200,8 +208,14 @@ __device__ __forceinline__ void clear_words(const ClearWords& z) {
         z.at[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// With one bucket a fragment: bound by its streams (92 to 104 bytes a
+// fragment, 5 TB/s).  With four: by the latency of the gathers at the wavefronts
+// that fit, so the registers are held to 128 (FP8 RGBA took 148, three
+// wavefronts a SIMD): 8.4M fragments, FP8 RGBA, 418 -> 404 us with 1139 vector
+// instructions instead of 1351, 390 with four wavefronts.  Keeping fewer
+// decoded taps (99 registers, 1315 instructions) gains no fifth.
 template <int FMT, int C, int MODE>
-__global__ __launch_bounds__(256) void k_bwd_fragment(
+__global__ __launch_bounds__(256, 4) void k_bwd_fragment(
     TexView t, const float* __restrict__ uv, const float* __restrict__ tbn,
     const float* __restrict__ view, const float* __restrict__ grad_out,
     float* __restrict__ grad_view, float* __restrict__ grad_uv, uint32_t* __restrict__ keys,
@@ -251,8 +265,7 @@ __global__ __launch_bounds__(256) void k_bwd_fragment(
     if constexpr (MODE == MODE_NEAREST) {
         int i = bucket_of(g.u, t.W), j = bucket_of(g.v, t.H);
         int64_t b = (int64_t)j * t.W + i;
-        float lv;
-        if (grad_view) bucket_grads<FMT, C>(t, b, p, go, gsx, gsy, lv);
+        if (grad_view) bucket_grads<FMT, C>(t, b, p, go, gsx, gsy);
         // no store before the taps have arrived: one counter tracks a
         // wavefront's loads and stores in order, so a wait for loads issued
         // after stores waits for those too
@@ -390,8 +403,7 @@ __global__ __launch_bounds__(256) void k_lod_bwd_fragment(
         if constexpr (MODE == MODE_NEAREST) {
             const int i = bucket_of(fr.u, t.W), j = bucket_of(fr.v, t.H);
             const int64_t b = (int64_t)j * t.W + i;
-            float lv;
-            if (grad_view) bucket_grads<FMT, C>(t, b, p, go, gsx, gsy, lv);
+            if (grad_view) bucket_grads<FMT, C>(t, b, p, go, gsx, gsy);
             if (rec) {
                 keys[u] = ((uint32_t)(off + b) << cell_bits) | cell;
                 ((float2*)wrec)[u] = make_float2(p.fx, p.fy);

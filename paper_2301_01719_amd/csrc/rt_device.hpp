@@ -88,6 +88,14 @@ __device__ __forceinline__ float e4m3_div256(uint32_t byte) {
     return (float)__builtin_bit_cast(_Float16, (unsigned short)h);
 }
 
+// The codes in bytes 1 and 3 of a word, as e4m3_div256 decodes them (three
+// integer operations for both).
+__device__ __forceinline__ void e4m3_div256_odd(uint32_t w, float& one, float& three) {
+    const uint32_t h = (w & 0x80008000u) | ((w >> 1) & 0x3F803F80u);
+    one = (float)__builtin_bit_cast(_Float16, (unsigned short)h);
+    three = (float)__builtin_bit_cast(_Float16, (unsigned short)(h >> 16));
+}
+
 struct F4 {
     float v[4];
 };
@@ -208,6 +216,14 @@ struct RowBits {
     }
     // the values as load_texel gives them
     __device__ __forceinline__ void decode(F4& a, F4& b) const {
+        float code[4 * WORDS];  // FP8
+        if constexpr (FMT == FMT_FP8) {
+#pragma unroll
+            for (int k = 0; k < WORDS; k++) {
+                e4m3_div256_odd(w[k] << 8, code[4 * k], code[4 * k + 2]);
+                e4m3_div256_odd(w[k], code[4 * k + 1], code[4 * k + 3]);
+            }
+        }
 #pragma unroll
         for (int e = 0; e < 8; e++) {
             float v = 0.f;
@@ -215,7 +231,7 @@ struct RowBits {
                 const int k = e / 4 * C + e % 4;
                 if constexpr (FMT == FMT_F32) v = __uint_as_float(w[k]);
                 else if constexpr (FMT == FMT_BF16) v = (k & 1) ? bf16_hi(w[k / 2]) : bf16_lo(w[k / 2]);
-                else v = e4m3_div256((w[k / 4] >> (8 * (k & 3))) & 0xFFu);
+                else v = code[k];
             }
             (e < 4 ? a : b).v[e % 4] = v;
         }
@@ -227,7 +243,7 @@ struct RowBits {
 // waited for.  Two texels of a row by one access halve the instructions of a
 // gather, which is bound by the lines that each of them touches (64 when every
 // lane reads another bucket).  Four buckets, 8.4M fragments of an FP8 RGBA
-// texture: lookup 511 -> 284 us, fragment pass of the backward 509 -> 418;
+// texture: lookup 511 -> 284 us, fragment pass of the backward 509 -> 418 (390 with the rest of it shortened);
 // 2.1M fragments of a BF16 RGBA one: lookup 205 -> 155.  One bucket: the same
 // to 5% less.
 template <int FMT, int C, int NB>
@@ -486,6 +502,16 @@ __device__ __forceinline__ Foot footprint(float sx, float sy, int n) {
     return p;
 }
 
+// k mod W in [0, W).  A wavefront with every k there already (a texture that
+// does not repeat) skips the division, about 20 instructions.
+__device__ __forceinline__ int wrap(int k, int W) {
+    if ((uint32_t)k >= (uint32_t)W) {
+        k %= W;
+        k = k < 0 ? k + W : k;
+    }
+    return k;
+}
+
 // Bucket column (or row) of a texture coordinate: floor(frac(u) W) with the UV
 // plane repeating.  It is evaluated as floor(u W) mod W, which is the same
 // integer, because u W is exact for a power-of-two W whereas frac(u) = u + 1
@@ -494,8 +520,7 @@ __device__ __forceinline__ Foot footprint(float sx, float sy, int n) {
 __device__ __forceinline__ int bucket_of(float u, int W) {
     const float fq = floorf(u * (float)W);
     if (!(fabsf(fq) < 1073741824.0f)) return 0;
-    const int i = (int)fq % W;
-    return i < 0 ? i + W : i;
+    return wrap((int)fq, W);
 }
 
 // Bilinear-bucket footprint in UV: p = frac(u) W - 1/2, columns floor(p) and
@@ -523,8 +548,7 @@ __device__ __forceinline__ void bucket_pair(float u, int W, int& i0, int& i1, fl
         a = r + 0.5f;
         k -= 1;
     }
-    k %= W;
-    i0 = k < 0 ? k + W : k;
+    i0 = wrap(k, W);
     i1 = i0 + 1 == W ? 0 : i0 + 1;
 }
 
