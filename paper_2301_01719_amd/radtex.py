@@ -146,12 +146,24 @@ def _check(status: int):
         raise RadtexError(status, msg)
 
 
+# Addresses and streams are passed as plain integers (every argument that takes
+# one is declared c_void_p).  A lookup of 4096 fragments is bound by this file and
+# the launch (3.7 us of it): 10.1 us a call with the stream object and the
+# fragments' checks written in one loop, 7.4 so.
+
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(device) -> int:
+    """The current stream of a device, without building the stream object where
+    torch gives its handle (0.1 us, 2.1 with the object)."""
+    if _raw_stream is not None and isinstance(device, torch.device) and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _need_gpu(t: torch.Tensor, name: str, dtype=None):
@@ -273,15 +285,23 @@ def _frags(uv, tbn, view, image=None) -> Fragments:
     images (a tiling hint, checked by the library); None: a flat list.  view
     may be None where the entry point does not read it."""
     N = uv.shape[0]
-    for t, name, shape in ((uv, "uv", (N, 2)), (tbn, "tbn", (N, 3, 3)), (view, "view", (N, 3))):
-        if t is None and name == "view":
-            continue
-        _need_gpu(t, name, torch.float32)
-        if tuple(t.shape) != shape and not (name == "tbn" and tuple(t.shape) == (N, 9)):
-            raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shape}")
+    _need_gpu(uv, "uv", torch.float32)
+    if uv.shape != (N, 2):
+        raise _bad_shape(uv, "uv", (N, 2))
+    _need_gpu(tbn, "tbn", torch.float32)
+    if tbn.shape != (N, 3, 3) and tbn.shape != (N, 9):
+        raise _bad_shape(tbn, "tbn", (N, 3, 3))
+    if view is not None:
+        _need_gpu(view, "view", torch.float32)
+        if view.shape != (N, 3):
+            raise _bad_shape(view, "view", (N, 3))
     v, h, w = image if image is not None else (0, 0, 0)
     return Fragments(N, v, h, w, uv.data_ptr(), tbn.data_ptr(),
                      None if view is None else view.data_ptr())
+
+
+def _bad_shape(t, name, shape) -> ValueError:
+    return ValueError(f"{name} has shape {tuple(t.shape)}, expected {shape}")
 
 
 def quantize(tex: Texture, fmt: str):
