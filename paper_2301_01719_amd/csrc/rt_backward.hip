@@ -1194,52 +1194,69 @@ __device__ __forceinline__ void accumulate_round(int cell, float v[4 * C], bool 
     }
 }
 
-// A sorted record as loaded: its key, its bilinear fractions and its upstream
-// gradient times the bucket weight (1 in nearest mode).
-template <int C>
+// A sorted record's key and its number (in the order of the fragments): where
+// the rest of it is gathered from.
+struct RecIndex {
+    uint32_t key, rec;
+};
+
+__device__ __forceinline__ void load_index(const uint32_t* __restrict__ skeys,
+                                           const uint32_t* __restrict__ svals, int64_t i,
+                                           RecIndex& r) {
+    r.key = skeys[i];
+    r.rec = svals ? svals[i] : (uint32_t)i;
+}
+
+// A record as loaded, nothing computed from it yet (that would wait for it): its
+// bilinear fractions, in bilinear-bucket mode those of its bucket too, and its
+// upstream gradient.
+template <int C, int MODE>
 struct RawRec {
-    uint32_t key;
-    float fx, fy;
+    RecIndex at;
+    float w[MODE == MODE_NEAREST ? 2 : 4];
     float g[C];
 };
 
 template <int C, int MODE>
-__device__ __forceinline__ void load_raw(const uint32_t* __restrict__ skeys,
-                                         const uint32_t* __restrict__ svals,
-                                         const float* __restrict__ wrec,
-                                         const float* __restrict__ grad_out, int64_t i,
-                                         RawRec<C>& r) {
-    r.key = skeys[i];
-    const uint32_t rec = svals ? svals[i] : (uint32_t)i;
-    float wb = 1.f;
+__device__ __forceinline__ void load_raw(const float* __restrict__ wrec,
+                                         const float* __restrict__ grad_out, const RecIndex& at,
+                                         RawRec<C, MODE>& r) {
+    r.at = at;
     int64_t frag;
     if constexpr (MODE == MODE_NEAREST) {
-        frag = rec;
+        frag = at.rec;
         const float2 w2 = ((const float2*)wrec)[frag];
-        r.fx = w2.x;
-        r.fy = w2.y;
+        r.w[0] = w2.x;
+        r.w[1] = w2.y;
     } else {
-        frag = rec >> 2;
-        const int k = rec & 3;
+        frag = at.rec >> 2;
         const float4 w4 = ((const float4*)wrec)[frag];
-        r.fx = w4.x;
-        r.fy = w4.y;
-        const float aa = w4.z, bb = w4.w;
+        r.w[0] = w4.x;
+        r.w[1] = w4.y;
+        r.w[2] = w4.z;
+        r.w[3] = w4.w;
+    }
+#pragma unroll
+    for (int c = 0; c < C; c++) r.g[c] = grad_out[frag * C + c];
+}
+
+// The four tap contributions of a loaded record: v = (w00, w01, w10, w11) x its
+// upstream gradient times its bucket's weight (1 in nearest mode).
+template <int C, int MODE>
+__device__ __forceinline__ void expand_raw(const RawRec<C, MODE>& r, float v[4 * C]) {
+    const float fx = r.w[0], fy = r.w[1];
+    const float w00 = (1.f - fx) * (1.f - fy), w01 = fx * (1.f - fy);
+    const float w10 = (1.f - fx) * fy, w11 = fx * fy;
+    float wb = 1.f;
+    if constexpr (MODE == MODE_BILINEAR) {
+        const int k = r.at.rec & 3;
+        const float aa = r.w[2], bb = r.w[3];
         wb = (k == 0) ? (1.f - aa) * (1.f - bb)
                       : (k == 1) ? aa * (1.f - bb) : (k == 2) ? (1.f - aa) * bb : aa * bb;
     }
 #pragma unroll
-    for (int c = 0; c < C; c++) r.g[c] = grad_out[frag * C + c] * wb;
-}
-
-// The four tap contributions of a loaded record: v = (w00, w01, w10, w11) x g.
-template <int C>
-__device__ __forceinline__ void expand_raw(const RawRec<C>& r, float v[4 * C]) {
-    const float w00 = (1.f - r.fx) * (1.f - r.fy), w01 = r.fx * (1.f - r.fy);
-    const float w10 = (1.f - r.fx) * r.fy, w11 = r.fx * r.fy;
-#pragma unroll
     for (int c = 0; c < C; c++) {
-        const float gc = r.g[c];
+        const float gc = r.g[c] * wb;
         v[0 * C + c] = w00 * gc;
         v[1 * C + c] = w01 * gc;
         v[2 * C + c] = w10 * gc;
@@ -1494,11 +1511,14 @@ __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ ske
 // and slot 1 for the last.  They return at once when k_segacc saw no such
 // bucket.
 //
-// Bound by vector issue (73% of the cycles on the 64 views' 67M records, 269
-// vector and 30 LDS instructions a round; 326 and 57, with six times the bank
-// conflicts, when rounds scanned whole runs and carried the last one): 64 views
-// 973 -> 718 us, 8 views with bilinear buckets (33.5M records, gathered)
-// 600 -> 520 us, 2867 buckets of 70 records 39 -> 10.5 us (their lists).
+// Bound by vector issue (87% of the cycles on the 64 views' 67M records, about
+// 265 vector instructions a round, 58% with bilinear buckets).  64 views: 973 us
+// when rounds scanned whole runs and carried the last one, 718 without the
+// carry, 655 since no round waits for a list entry, a range or an index.  8 views
+// with bilinear buckets (33.5M records, gathered): 600, 530, 520; 2867 buckets of
+// 70 records: 39 us, 10.5 (more lists).  Six wavefronts a SIMD instead of five
+// (80 registers, one spilled) give 638 us on the 64 views, but a launch that has
+// scratch costs a small backward 7 us.
 template <int C, int MODE>
 __global__ __launch_bounds__(256) void k_segacc_big(const uint32_t* __restrict__ skeys,
                                                     const uint32_t* __restrict__ svals,
@@ -1527,46 +1547,53 @@ __global__ __launch_bounds__(256) void k_segacc_big(const uint32_t* __restrict__
     float* tile = lds + w * te;
     // the wavefront's work items: entries [item, items) of its list in steps of
     // `stride`, or the (at most two) slots of its chunk
+    const int lane = threadIdx.x & 63;
     uint32_t item, items, stride;
     const uint32_t* entries = nullptr;
     int c0 = 0, c1 = 0;
-    uint32_t b_next = 0, b_last = 0;
-    int2 r_next = make_int2(0, 0);
+    uint32_t b_first = 0, b_last = 0;  // of the chunk
     if (!hot) {
         const uint32_t list = blockIdx.x % BIG_LISTS;
         stride = big_blocks / BIG_LISTS * 4;
         item = blockIdx.x / BIG_LISTS * 4 + w;
         items = __builtin_amdgcn_readfirstlane(big_count[list * BIG_STRIDE]);
         entries = big_list + list * big_cap;
-        if (item < items) b_next = __builtin_amdgcn_readfirstlane(entries[item]);
     } else {
         const int64_t first = ((int64_t)(blockIdx.x - big_blocks) * 4 + w) * PIECE;
         if (first >= R) return;
         c0 = (int)first;
         c1 = (int)((first + PIECE < R) ? first + PIECE : R);
-        b_next = __builtin_amdgcn_readfirstlane(skeys[c0]) >> cell_bits;
+        b_first = __builtin_amdgcn_readfirstlane(skeys[c0]) >> cell_bits;
         b_last = __builtin_amdgcn_readfirstlane(skeys[c1 - 1]) >> cell_bits;
         // records past the last bucket (sparse plans) belong to no slot
         stride = 1;
         item = 0;
-        items = b_next >= nb ? 0u : b_last == b_next || b_last >= nb ? 1u : 2u;
+        items = b_first >= nb ? 0u : b_last == b_first || b_last >= nb ? 1u : 2u;
     }
-    if (item < items) r_next = range[b_next];
     // the next item: `left` records of one bucket from record `at` on, their
-    // tile to dst.  Its successor's bucket and range are read ahead.
+    // tile to dst.  The buckets and ranges of 64 items are held, one per lane, so
+    // that an item waits for neither.
     struct Item {
         int at, left;
         float* dst;
     };
+    int held = 64;  // the next item's lane; 64: read the next 64
+    uint32_t hb = 0;
+    int2 hr = make_int2(0, 0);
     auto next_item = [&](Item& k) {
         for (; item < items; item += stride) {
-            const uint32_t b = b_next;
-            int a = __builtin_amdgcn_readfirstlane(r_next.x);
-            int e = __builtin_amdgcn_readfirstlane(r_next.y);
-            if (item + stride < items) {
-                b_next = hot ? b_last : __builtin_amdgcn_readfirstlane(entries[item + stride]);
-                r_next = range[b_next];
+            if (held == 64) {
+                const uint32_t q = item + lane * stride;
+                if (q < items) {
+                    hb = !hot ? entries[q] : q == 0 ? b_first : b_last;
+                    hr = range[hb];
+                }
+                held = 0;
             }
+            const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)hb, held);
+            int a = __builtin_amdgcn_readlane(hr.x, held);
+            int e = __builtin_amdgcn_readlane(hr.y, held);
+            held++;
             if (hot) {
                 if (e - a <= PIECE) continue;
                 a = a > c0 ? a : c0;
@@ -1583,41 +1610,47 @@ __global__ __launch_bounds__(256) void k_segacc_big(const uint32_t* __restrict__
         }
         return false;
     };
-    // Rounds of 64 records.  The next round's records, of this bucket or of the
-    // next item, are loaded while this round is summed and before the tile is
-    // stored: on gfx950 one counter tracks a wavefront's loads and stores, so
-    // loads after the stores would wait for them.
-    Item cur_item, nxt_item{};
+    // the round after `k`: the item's next records, or the next item
+    auto next_round = [&](const Item& k, Item& next) {
+        if (k.left <= 64) return next_item(next);
+        next.at = k.at + 64;
+        next.left = k.left - 64;
+        next.dst = k.dst;
+        return true;
+    };
+    // Rounds of 64 records.  While a round is summed, and before its tile is
+    // stored, the next round's records are gathered and the indices of the one
+    // after that are loaded, so no round waits for an index.  (On gfx950 one
+    // counter tracks a wavefront's loads and stores: loads after the stores
+    // would wait for them.)
+    Item cur_item, nxt_item{}, far_item{};
     if (!next_item(cur_item)) return;
-    const int lane = threadIdx.x & 63;
-    RawRec<C> cur{}, nxt{};
-    if (lane < cur_item.left)
-        load_raw<C, MODE>(skeys, svals, wrec, grad_out, cur_item.at + lane, cur);
+    RecIndex cur_at{}, nxt_at{}, far_at{};
+    if (lane < cur_item.left) load_index(skeys, svals, cur_item.at + lane, cur_at);
+    bool more = next_round(cur_item, nxt_item);
+    if (more && lane < nxt_item.left) load_index(skeys, svals, nxt_item.at + lane, nxt_at);
+    RawRec<C, MODE> cur{}, nxt{};
+    if (lane < cur_item.left) load_raw<C, MODE>(wrec, grad_out, cur_at, cur);
     tile_zero(tile, te);
     for (;;) {
-        const bool ends = cur_item.left <= 64;
-        bool more = true;
-        if (ends) {
-            more = next_item(nxt_item);
-        } else {
-            nxt_item.at = cur_item.at + 64;
-            nxt_item.left = cur_item.left - 64;
-            nxt_item.dst = cur_item.dst;
-        }
-        if (more && lane < nxt_item.left)
-            load_raw<C, MODE>(skeys, svals, wrec, grad_out, nxt_item.at + lane, nxt);
+        if (more && lane < nxt_item.left) load_raw<C, MODE>(wrec, grad_out, nxt_at, nxt);
+        const bool after = more && next_round(nxt_item, far_item);
+        if (after && lane < far_item.left) load_index(skeys, svals, far_item.at + lane, far_at);
         const bool valid = lane < cur_item.left;
         float v[4 * C];
-        expand_raw<C>(cur, v);
-        const int cell = valid ? (int)(cur.key & cell_mask) : -2 - lane;
+        expand_raw<C, MODE>(cur, v);
+        const int cell = valid ? (int)(cur.at.key & cell_mask) : -2 - lane;
         accumulate_round<C>(cell, v, valid, n, row_inv, tile);
-        if (ends) {
+        if (cur_item.left <= 64) {
             tile_store(tile, cur_item.dst, te);
             if (!more) return;
             tile_zero(tile, te);
         }
         cur = nxt;
         cur_item = nxt_item;
+        nxt_at = far_at;
+        nxt_item = far_item;
+        more = after;
     }
 }
 
