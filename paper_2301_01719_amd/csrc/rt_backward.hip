@@ -14,11 +14,11 @@
 //                       keep record order, so the sorted sequence depends only
 //                       on the inputs.
 //   3. k_bucket_ranges  [start, end) of every bucket in the sorted records.
-//      k_payload        (buckets of at most 64 records on average, in its
+//      k_payload        (buckets of at most 8 records on average, in its
 //                       place) the same, and the fractions and weighted
 //                       upstream gradient of the records of buckets with at
 //                       most 64 records, written in sorted order.
-//   4. k_segacc         eight buckets per wavefront (pass 1): the records of a
+//   4. k_segacc         four or eight buckets per wavefront (pass 1): the records of a
 //                       bucket with at most 64 are held in a register window
 //                       (read from the payload, or gathered from the
 //                       fragments) and reduced per cell by a segmented scan
@@ -1414,11 +1414,10 @@ __device__ __forceinline__ void zero_store(float* __restrict__ dst, int te) {
 // pass 1: each wavefront owns G consecutive buckets (their ranges come in one
 // coalesced load) and writes their tiles one after the other, so the stores
 // of untouched buckets are issued back to back; four wavefronts per
-// workgroup.  G = SEG_GROUP (8), or 4 when the records are read from the
-// sorted payload (shorter groups spread the buckets over more wavefronts once
-// the window loads are cheap).  k_segacc writes the untouched buckets and those with at most 64
-// records (served from one register window) and lists those with 65..PIECE
-// records for k_segacc_big (rounds of 64).  Splitting keeps the
+// workgroup.  G = 4, or SEG_GROUP (8) where most buckets are only listed (see
+// launch_accumulate).  k_segacc writes the untouched buckets and those with at
+// most 64 records (served from one register window) and lists those with
+// 65..PIECE records for k_segacc_big (rounds of 64).  Splitting keeps the
 // register footprint of the common case small.  The list is split over
 // BIG_LISTS counters, one atomic per group, so that workloads where most
 // buckets are big do not serialise on one address: runs of 2^big_run_log
@@ -2066,10 +2065,13 @@ hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, cons
     if (R > 0) dis = launch_sort_records(plan, ws, range, s, &skeys, &svals);
 
     // 3. ranges of the sorted records, with the records' payload in sorted
-    // order when buckets hold 64 records or fewer on average (most records
-    // then go through the register window); both return at once when the sort
-    // did
-    const bool pay = R > 0 && R <= 64 * nb;
+    // order when buckets hold 8 records or fewer on average: a window of 64
+    // records then serves several buckets, of which each would gather again;
+    // both return at once when the sort did.  Payload, windows and big pass
+    // against ranges, windows and big pass, us: 2 records a bucket 756 and 788;
+    // 12: 317 and 299; 20: 70 and 63; 23 (random rays): 96 and 99; 48: 140 and
+    // 135; 64 (RGB): 133 and 95; 32 with bilinear buckets: 397 and 353.
+    const bool pay = R > 0 && R <= 8 * nb;
     if (R > 0 && !pay) {
         prof_begin(K_BUCKET_RANGES, s);
         hipLaunchKernelGGL(k_bucket_ranges, dim3((uint32_t)((R + 1023) / 1024)), dim3(256), 0, s,
@@ -2086,28 +2088,33 @@ hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, cons
     }
     const int te = (int)plan.tile_elems;
     const uint32_t cell_mask = plan.cell_bits >= 32 ? 0xFFFFFFFFu : ((1u << plan.cell_bits) - 1u);
-    // the big-bucket lists' capacity (planned for SEG_GROUP) also holds the
-    // lists of groups of 4: ceil(2x) <= 2 ceil(x) runs of half the buckets
-    const int G = pay ? 4 : SEG_GROUP;
+    // Buckets per wavefront: 4, so that more wavefronts share the windows' loads
+    // (us with 8 and with 4: 20 records a bucket 57 and 50, 48: 100 and 86, 64: 50
+    // and 43, 128 with bilinear buckets 165 and 153, 2867 buckets of 70: 22 and
+    // 15), unless nearly all buckets go to the big pass and are only listed here
+    // (256: 48 and 61).  The big-bucket lists' capacity (planned for SEG_GROUP)
+    // also holds the lists of groups of 4: a run covers as many buckets.
+    const int G = R <= 128 * nb ? 4 : SEG_GROUP;
     const int64_t groups = (nb + G - 1) / G;
-    // Consecutive groups that append to one big-bucket list: BIG_RUN where that
-    // gives every list several runs, fewer for fewer groups, so that all lists
-    // (and with them all of the big pass's workgroups) get work.  With BIG_RUN
-    // throughout, the 2867 buckets of a 61 x 47 matrix went to 6 of the 64
+    // Consecutive groups that append to one big-bucket list: BIG_RUN (of
+    // SEG_GROUP buckets) where that gives every list several runs, fewer for fewer
+    // groups, so that all lists (and with them all of the big pass's workgroups)
+    // get work.  With BIG_RUN throughout, the 2867 buckets of a 61 x 47 matrix went to 6 of the 64
     // lists and the pass took 38 us.  Powers of two up to BIG_RUN keep the lists
     // within the capacity planned for BIG_RUN.
     int run_log = 0;
-    while ((2 << run_log) <= BIG_RUN && (groups >> (run_log + 1)) >= 4 * BIG_LISTS) run_log++;
+    while ((G << (run_log + 1)) <= BIG_RUN * SEG_GROUP &&
+           (groups >> (run_log + 1)) >= 4 * BIG_LISTS) run_log++;
     // the workgroups stride over the groups, so at most 2^20 of them keep the
     // launch within one dispatch (2^28 buckets and more at small n)
     const dim3 g1((uint32_t)std::min<int64_t>((groups + 3) / 4, int64_t(1) << 20));
     const float* pf = pay ? payf : nullptr;
     prof_begin(K_SEGACC, s);
     if (mode == MODE_NEAREST) {
-        if (pay) launch_segacc_c<MODE_NEAREST, 4>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
+        if (G == 4) launch_segacc_c<MODE_NEAREST, 4>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
         else launch_segacc_c<MODE_NEAREST, SEG_GROUP>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
     } else {
-        if (pay) launch_segacc_c<MODE_BILINEAR, 4>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
+        if (G == 4) launch_segacc_c<MODE_BILINEAR, 4>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
         else launch_segacc_c<MODE_BILINEAR, SEG_GROUP>(C, g1, (size_t)4 * te * 4, s, skeys, svals, wrec, grad_out, pf, payg, range, out, nb, R, n, cell_mask, big_count, big_list, plan.big_cap, run_log, keys0, dis);
     }
     prof_end(K_SEGACC, s);

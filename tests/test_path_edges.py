@@ -1,0 +1,173 @@
+"""The lines between the library's kernels: small and large sorts, the payload
+and the gathered windows, the accumulation's bucket sizes, the cleared words, the
+scatter of a dictionary update and the cached light lookup, each at the sizes on
+both sides of where one form takes over from another, against the oracle.
+
+Tolerances: the texel gradient is checked per element as in the parity tests
+(1e-4 of the summed magnitudes, plus the rounding of the weights); planned and
+unplanned nearest gradients are equal bit for bit; a dictionary entry is a sum in
+pieces of 64 rows, so it moves by at most (64 + pieces + 2) roundings of the
+largest value; light lookups are within the forward's 1e-5.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import away_from_edges, bucket_edge_mask, check_fwd, check_grad_tex, host
+from test_shadow import _bit_texture, _frags, _light_vecs
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+ORACLE_MODE = {"nearest": oracle.MODE_NEAREST, "bilinear": oracle.MODE_BILINEAR}
+
+
+@pytest.fixture(scope="module")
+def rt():
+    from paper_2301_01719_amd import radtex
+    return radtex
+
+
+def _views(g, N, spread=1.0):
+    v = torch.randn((N, 3), generator=g) * spread
+    v[:, 2] = 1.0 + 0.1 * torch.rand(N, generator=g)
+    return v
+
+
+def _away(uv, view, W, H, n, mode, count):
+    """The first `count` fragments away from every cell edge."""
+    tbn = torch.eye(3).expand(uv.shape[0], 3, 3).contiguous()
+    keep = away_from_edges(uv.numpy(), tbn.numpy(), view.numpy(), W, H, n, mode)
+    k = torch.from_numpy(np.nonzero(keep)[0][:count])
+    assert len(k) == count
+    return uv[k].contiguous(), tbn[:count].contiguous(), view[k].contiguous()
+
+
+def _check_backward(rt, uv, tbn, view, W, H, n, C, mode, seed):
+    N = uv.shape[0]
+    tex = rt.Texture(torch.zeros((H, W, n, n, C), device=DEV), W, H, n, C)
+    go = torch.randn((N, C), generator=torch.Generator().manual_seed(seed))
+    d = [x.to(DEV) for x in (uv, tbn, view, go)]
+    gt, _, _ = rt.lookup_bwd(tex, *d, mode=mode, want_view=False, want_uv=False)
+    torch.cuda.synchronize()
+    otex = oracle.Tex(np.zeros((H, W, n, n, C), np.float32), W, H, n, C)
+    ref = oracle.lookup_bwd(otex, uv.numpy(), tbn.numpy(), view.numpy(), go.numpy(),
+                            mode=ORACLE_MODE[mode])
+    check_grad_tex(host(gt), ref, n)
+    if mode == "nearest":
+        order, *p = rt.plan_fragments(tex, *d[:3], mode=mode)
+        pt, _, _ = rt.lookup_bwd(tex, *p, d[3][order.long()].contiguous(), mode=mode,
+                                 want_view=False, want_uv=False)
+        assert torch.equal(pt, gt)
+
+
+# 16-bit keys sort by two 8-bit digits: 4 keys a thread up to 2^17 records, 8 up
+# to 2^18, 16 and scans of its own in the scatters up to 2^20.  19-bit keys by 10
+# and 9 bits: up to 2^15, 2^16 and 2^18.  (n = 13: cell bits that are no power of
+# two.)
+@pytest.mark.parametrize("W,H,n,C,N,mode", [
+    (16, 16, 16, 1, 1, "nearest"), (16, 16, 16, 2, 1023, "nearest"),
+    (16, 16, 16, 3, 1025, "nearest"), (16, 16, 16, 1, 1 << 17, "nearest"),
+    (16, 16, 16, 4, (1 << 17) + 1, "nearest"), (16, 16, 16, 1, 1 << 18, "nearest"),
+    (16, 16, 16, 1, (1 << 18) + 1, "nearest"), (16, 16, 16, 1, 1 << 20, "nearest"),
+    (16, 16, 16, 1, (1 << 20) + 1, "nearest"), (16, 16, 16, 2, 1 << 15, "bilinear"),
+    (16, 16, 16, 3, (1 << 15) + 1, "bilinear"), (64, 32, 13, 3, 1 << 15, "nearest"),
+    (64, 32, 13, 1, (1 << 15) + 1, "nearest"), (64, 32, 13, 4, (1 << 16) + 1, "nearest"),
+    (64, 32, 13, 1, 1 << 18, "nearest"), (64, 32, 13, 1, (1 << 18) + 1, "nearest"),
+    (64, 32, 13, 2, (1 << 16) + 1, "bilinear")])
+def test_sorts_of_either_side_of_their_limits(rt, W, H, n, C, N, mode):
+    g = torch.Generator().manual_seed(N + n)
+    M = N + N // 8 + 64
+    f = _away(torch.rand((M, 2), generator=g) * 2 - 0.5, _views(g, M), W, H, n, mode, N)
+    _check_backward(rt, *f, W, H, n, C, mode, N)
+
+
+# A payload is written up to 8 records a bucket on average.
+@pytest.mark.parametrize("C", [1, 2, 3, 4])
+@pytest.mark.parametrize("N,mode", [(8 * 2048, "nearest"), (8 * 2048 + 1, "nearest"),
+                                    (2 * 2048, "bilinear"), (2 * 2048 + 1, "bilinear")])
+def test_payload_and_gathered_windows(rt, C, N, mode):
+    W, H, n = 64, 32, 8
+    g = torch.Generator().manual_seed(N + C)
+    M = N + N // 8 + 64
+    uv = torch.rand((M, 2), generator=g)
+    uv[: N // 4] = (uv[: N // 4] * 0.8 + 3.1) / torch.tensor([W, H])  # one bucket of many
+    f = _away(uv, _views(g, M), W, H, n, mode, N)
+    _check_backward(rt, *f, W, H, n, C, mode, N)
+
+
+# Buckets around a window (64), a round and a piece (2048); directions spread
+# over the cells (short runs) or gathered in one (a run of the whole bucket).
+@pytest.mark.parametrize("spread", [1.0, 1e-4])
+@pytest.mark.parametrize("C", [1, 2, 3, 4])
+@pytest.mark.parametrize("W,H", [(4, 2), (48, 32)])
+@pytest.mark.parametrize("mode", ["nearest", "bilinear"])
+def test_buckets_of_every_size(rt, W, H, C, spread, mode):
+    n = 9
+    counts = [64, 65, 128, 129, 2048, 2049, 1, 4200]
+    g = torch.Generator().manual_seed(C)
+    fr = []
+    for b, count in enumerate(counts):
+        M = count + count // 8 + 32
+        jitter = torch.rand((M, 2), generator=g) * 0.6 + 0.2
+        uv = (torch.tensor([b % W, b // W]) + jitter) / torch.tensor([W, H])
+        view = _views(g, M, spread)
+        if spread < 1:
+            view[:, :2] += torch.tensor([0.31, 0.17])  # inside one cell
+        fr.append(_away(uv, view, W, H, n, mode, count))
+    uv, tbn, view = (torch.cat([f[k] for f in fr]) for k in range(3))
+    p = torch.randperm(sum(counts), generator=g)
+    _check_backward(rt, uv[p].contiguous(), tbn, view[p].contiguous(), W, H, n, C, mode, C)
+
+
+# Few fragments over many buckets (the ranges are cleared by a launch of their
+# own) and enough of them (cleared by the launch that makes the records).
+@pytest.mark.parametrize("N", [1, 3, 2000, 40000])
+def test_words_cleared_for_few_and_many_fragments(rt, N):
+    W, H, n = 512, 256, 2
+    g = torch.Generator().manual_seed(N)
+    f = _away(torch.rand((2 * N + 64, 2), generator=g), _views(g, 2 * N + 64), W, H, n, "nearest", N)
+    _check_backward(rt, *f, W, H, n, 1, "nearest", N)
+
+
+# The scatter's digit has 8, 10 or 12 bits; M on both sides of a wavefront and a
+# tile of rows.
+@pytest.mark.parametrize("M", [1, 64, 65, 1025, 6000])
+@pytest.mark.parametrize("K", [1, 255, 256, 257, 1024, 1025, 4096])
+def test_update_of_few_and_many_entries(rt, M, K):
+    D = 5
+    g = torch.Generator().manual_seed(M * 7 + K)
+    X = torch.randn((M, D), generator=g)
+    a = torch.randint(0, K, (M,), generator=g, dtype=torch.int32)
+    a[: M // 2] = K - 1  # one large entry, the last
+    prev = torch.randn((K, D), generator=g)
+    cb = prev.clone().to(DEV)
+    cnt = rt.vq_update(X.to(DEV), a.to(DEV), cb)
+    torch.cuda.synchronize()
+    ref, ref_cnt = oracle.vq_update(X.numpy(), a.numpy(), prev.numpy())
+    np.testing.assert_array_equal(host(cnt), ref_cnt)
+    np.testing.assert_array_equal(host(cb)[ref_cnt == 0], prev.numpy()[ref_cnt == 0])
+    tol = (64 + np.ceil(ref_cnt / 64.0) + 2)[:, None] * 2.0 ** -24 * np.abs(X.numpy()).max()
+    assert np.all(np.abs(host(cb) - ref) <= tol)
+
+
+# The words of a bucket are cached up to n = 16; below n = 4 the taps of four
+# buckets would overlap; 16 x 16 flags are read 16 bytes at a time.
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 11, 15, 16, 17])
+@pytest.mark.parametrize("S", [3, 4, 6])
+@pytest.mark.parametrize("mode", ["nearest", "bilinear"])
+def test_light_lookup_with_and_without_the_cache(rt, n, S, mode):
+    W, H, N = 3, 2, 700
+    tex, otex = _bit_texture(rt, W, H, n, seed=n)
+    uv, tbn, _ = _frags(n * 10 + S, N)
+    vec = _light_vecs("directional", S, seed=n)
+    light = rt.make_light(vec.numpy(), "directional")
+    out = rt.lookup_light(tex, uv.to(DEV), tbn.to(DEV), light, mode=mode)
+    torch.cuda.synchronize()
+    ref = oracle.lookup_light(otex, uv.numpy(), tbn.numpy(), vec.numpy(),
+                              oracle.LIGHT_DIRECTIONAL, mode=ORACLE_MODE[mode])
+    keep = None
+    if mode == "nearest":
+        keep = bucket_edge_mask(uv.numpy(), tbn.numpy(), np.ones((N, 3), np.float32), W, H, n)
+    check_fwd(host(out), ref, keep)
