@@ -539,23 +539,55 @@ __global__ __launch_bounds__(256) void k_keys_in_order(const uint32_t* __restric
     if (range && !any && i0 < R) group_ranges(k, i0, R, cell_bits, nb, range);
 }
 
-// The order check of a small sort, on one radix tile of 256 IPT keys per
-// workgroup, which also counts the first pass's digits of its tile (the key's
-// lowest D bits) into counts[tile][digit], so that pass needs no launch of
-// k_radix_hist.
-template <int D, int IPT>
+// A tile's digit counts in LDS.  Neighbouring keys often have one digit (pixels
+// of one cell, records without a bucket), and LDS additions to one word run one
+// after the other, so the lanes count into COPIES = 4 tables, a quarter of the
+// banks apart.  A pass over 16.6M records of two views 28.8 us, 25.3 with 16-byte
+// loads, 20.1 with two tables, 17.0 with four, 16.3 with eight (twice the LDS);
+// 4.1M records of a mip chain, half of them without a bucket, 17.8 us, 9.6 with
+// four.
+template <int D>
+struct DigitCounts {
+    static constexpr int B = 1 << D, COPIES = 4, STRIDE = B + 64 / COPIES;
+    uint32_t at[COPIES * STRIDE];
+
+    __device__ __forceinline__ void clear() {
+        for (int d = threadIdx.x; d < COPIES * STRIDE; d += SORT_THREADS) at[d] = 0;
+    }
+    __device__ __forceinline__ void add(uint32_t digit) {  // its lowest D bits
+        atomicAdd(&at[threadIdx.x % COPIES * STRIDE + (digit & (B - 1))], 1u);
+    }
+    // to the table of all tiles: hist[d * tiles + tile], or with SMALL (a small
+    // sort, whose scatter adds the counts up itself) hist[tile * B + d]
+    template <bool SMALL>
+    __device__ __forceinline__ void store(uint32_t* __restrict__ hist, int64_t tile,
+                                          int64_t tiles) const {
+        for (int d = threadIdx.x; d < B; d += SORT_THREADS) {
+            uint32_t sum = 0;
+#pragma unroll
+            for (int c = 0; c < COPIES; c++) sum += at[c * STRIDE + d];
+            hist[SMALL ? tile * B + d : (int64_t)d * tiles + tile] = sum;
+        }
+    }
+};
+
+// The order check on one radix tile of 256 IPT keys per workgroup, which also
+// counts the first pass's digits of its tile (the key's lowest D bits) as
+// k_radix_hist does, so that pass needs no launch of it.
+template <int D, bool SMALL, int IPT>
 __global__ __launch_bounds__(256) void k_keys_in_order_hist(const uint32_t* __restrict__ keys,
                                                             int64_t R,
                                                             uint32_t* __restrict__ disorder,
                                                             int cell_bits, int64_t nb,
                                                             int2* __restrict__ range,
-                                                            uint32_t* __restrict__ counts) {
-    constexpr int B = 1 << D;
+                                                            uint32_t* __restrict__ hist,
+                                                            int64_t tiles) {
     constexpr int GROUPS = IPT / 4;
-    __shared__ uint32_t cnt[B];
+    __shared__ DigitCounts<D> cnt;
     const int t = threadIdx.x;
-    for (int d = t; d < B; d += 256) cnt[d] = 0;
-    const int64_t base = (int64_t)blockIdx.x * (256 * IPT) + t * 4;
+    cnt.clear();
+    const int64_t tile = xcd_block_id(blockIdx.x, gridDim.x);
+    const int64_t base = tile * (256 * IPT) + t * 4;
     uint32_t k[GROUPS][6];
     bool down = false;
 #pragma unroll
@@ -574,11 +606,11 @@ __global__ __launch_bounds__(256) void k_keys_in_order_hist(const uint32_t* __re
         if (i0 >= R) break;
 #pragma unroll
         for (int u = 0; u < 4; u++)
-            if (i0 + u < R) atomicAdd(&cnt[k[g][u + 1] & (B - 1)], 1u);
+            if (i0 + u < R) cnt.add(k[g][u + 1]);
         if (range && !any) group_ranges(k[g], i0, R, cell_bits, nb, range);
     }
     __syncthreads();
-    for (int d = t; d < B; d += 256) counts[(int64_t)blockIdx.x * B + d] = cnt[d];
+    cnt.template store<SMALL>(hist, tile, tiles);
 }
 
 // Digit counts of one tile of 256 IPT keys: hist[d * tiles + tile].  Tiles
@@ -586,26 +618,16 @@ __global__ __launch_bounds__(256) void k_keys_in_order_hist(const uint32_t* __re
 // neighbouring tiles share cache lines of the digit-major table, and so the
 // strided 4-byte stores of one XCD's tiles combine in its L2.  SMALL (a small
 // sort, whose scatter adds the counts up itself): tile-major, hist[tile * B + d].
-//
-// Neighbouring keys often have one digit (pixels of one cell, records without a
-// bucket), and LDS additions to one word run one after the other, so the lanes
-// count into COPIES = 4 tables, a quarter of the banks apart.  A pass over 16.6M
-// records of two views 28.8 us, 25.3 with 16-byte loads, 20.1 with two tables,
-// 17.0 with four, 16.3 with eight (twice the LDS); 4.1M records of a mip chain,
-// half of them without a bucket, 17.8 us, 9.6 with four.
 template <int D, bool SMALL, int IPT>
 __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(const uint32_t* __restrict__ keys,
                                                              int64_t R, int shift,
                                                              uint32_t* __restrict__ hist,
                                                              int64_t tiles,
                                                              const uint32_t* __restrict__ skip) {
-    constexpr int B = 1 << D;
-    constexpr int COPIES = 4, STRIDE = B + 64 / COPIES;
-    __shared__ uint32_t cnt[COPIES * STRIDE];
+    __shared__ DigitCounts<D> cnt;
     if (sort_skipped(skip)) return;
     const int t = threadIdx.x;
-    for (int d = t; d < COPIES * STRIDE; d += SORT_THREADS) cnt[d] = 0;
-    uint32_t* mine = cnt + t % COPIES * STRIDE;
+    cnt.clear();
     __syncthreads();
     const int64_t tile = xcd_block_id(blockIdx.x, gridDim.x);
     const int64_t base = tile * (SORT_THREADS * IPT);
@@ -621,15 +643,10 @@ __global__ __launch_bounds__(SORT_THREADS) void k_radix_hist(const uint32_t* __r
         const uint32_t q[4] = {k[r].x, k[r].y, k[r].z, k[r].w};
 #pragma unroll
         for (int u = 0; u < 4; u++)
-            if (i + u < R) atomicAdd(&mine[(q[u] >> shift) & (B - 1)], 1u);
+            if (i + u < R) cnt.add(q[u] >> shift);
     }
     __syncthreads();
-    for (int d = t; d < B; d += SORT_THREADS) {
-        uint32_t sum = 0;
-#pragma unroll
-        for (int c = 0; c < COPIES; c++) sum += cnt[c * STRIDE + d];
-        hist[SMALL ? tile * B + d : (int64_t)d * tiles + tile] = sum;
-    }
+    cnt.template store<SMALL>(hist, tile, tiles);
 }
 
 // x from the lane `o` below in the wavefront, for a power of two o < 64;
@@ -1979,22 +1996,28 @@ static void launch_radix_scatter(int D, const BwdPlan& plan, hipStream_t s, cons
     prof_end(K_RADIX_SCATTER, s);
 }
 
-// One pass of a small sort (the first one's digits are counted by the order
-// check, which is launched in place of the counting).
+// The digits of a pass counted, the first one's by the order check (`check`).
+template <bool SMALL, int IPT>
+static void launch_counts(int pass, bool check, int D, const BwdPlan& plan, hipStream_t s,
+                          const uint32_t* kin, uint32_t* hist, uint32_t* disorder, int2* range) {
+    if (pass == 0 && check) {
+        const dim3 grid((uint32_t)plan.tiles), block(SORT_THREADS);
+        prof_begin(K_ORDER_CHECK, s);
+        if (D == 8) hipLaunchKernelGGL((k_keys_in_order_hist<8, SMALL, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist, plan.tiles);
+        else if (D == 9) hipLaunchKernelGGL((k_keys_in_order_hist<9, SMALL, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist, plan.tiles);
+        else hipLaunchKernelGGL((k_keys_in_order_hist<10, SMALL, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist, plan.tiles);
+        prof_end(K_ORDER_CHECK, s);
+    } else {
+        launch_radix_hist<SMALL, IPT>(D, plan, s, kin, plan.digit_shift[pass], hist, disorder);
+    }
+}
+
+// One pass of a small sort.
 template <int IPT>
 static void launch_small_pass(int pass, int D, const BwdPlan& plan, hipStream_t s,
                               const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
                               uint32_t* vout, uint32_t* hist, uint32_t* disorder, int2* range) {
-    if (pass == 0) {
-        const dim3 grid((uint32_t)plan.tiles), block(SORT_THREADS);
-        prof_begin(K_ORDER_CHECK, s);
-        if (D == 8) hipLaunchKernelGGL((k_keys_in_order_hist<8, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist);
-        else if (D == 9) hipLaunchKernelGGL((k_keys_in_order_hist<9, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist);
-        else hipLaunchKernelGGL((k_keys_in_order_hist<10, IPT>), grid, block, 0, s, kin, plan.records, disorder, plan.cell_bits, plan.buckets, range, hist);
-        prof_end(K_ORDER_CHECK, s);
-    } else {
-        launch_radix_hist<true, IPT>(D, plan, s, kin, plan.digit_shift[pass], hist, disorder);
-    }
+    launch_counts<true, IPT>(pass, true, D, plan, s, kin, hist, disorder, range);
     launch_radix_scatter<true, IPT>(D, plan, s, kin, vin, kout, vout, plan.digit_shift[pass], hist,
                                     disorder);
 }
@@ -2006,9 +2029,14 @@ static void launch_small_pass(int pass, int D, const BwdPlan& plan, hipStream_t 
 // the check also writes the bucket ranges the keys give if they are in order.
 // The sorted keys and their record numbers end in *skeys, *svals.
 //
-// A small sort (see plan_backward) makes fewer launches: its order check counts
-// the first pass's digits, and its scatters add the counts up themselves (2
-// launches a pass, 1 for the first, instead of 4).
+// The order check counts the first pass's digits too where that costs ordered
+// keys no more than the launch it saves: up to COUNTING_CHECK records (check and
+// counts, us, ordered keys: 2.6M 25.5 and 23, 8.4M 36 and 34, 16.8M 43 and 49, 67M 96
+// and 124; unordered: 4.2M 31 and 28, 33.5M 142 and 137), and for a visit plan
+// (no ranges), whose keys are seldom ordered (16.6M: 85 and 73).  A small sort
+// (see plan_backward) makes fewer launches still: its scatters add the counts
+// up themselves (2 launches a pass, 1 for the first, instead of 4).
+constexpr int64_t COUNTING_CHECK = int64_t(1) << 23;
 static const uint32_t* launch_sort_records(const BwdPlan& plan, void* ws, int2* range,
                                            hipStream_t s, const uint32_t** skeys_out,
                                            const uint32_t** svals_out) {
@@ -2025,7 +2053,8 @@ static const uint32_t* launch_sort_records(const BwdPlan& plan, void* ws, int2* 
     const bool small = plan.small_sort;
     const uint32_t* kin = keys0;
     const uint32_t* vin = nullptr;
-    if (!small) {
+    const bool counting = small || !range || R <= COUNTING_CHECK;
+    if (!counting) {
         prof_begin(K_ORDER_CHECK, s);
         hipLaunchKernelGGL(k_keys_in_order, dim3((uint32_t)((R + 1023) / 1024)), dim3(256), 0, s,
                            keys0, R, disorder, plan.cell_bits, plan.buckets, range);
@@ -2044,7 +2073,7 @@ static const uint32_t* launch_sort_records(const BwdPlan& plan, void* ws, int2* 
             launch_small_pass<16>(pass, D, plan, s, kin, vin, kout, vout, hist, disorder, range);
         } else {
             const int64_t len = ((int64_t)1 << D) * plan.tiles;
-            launch_radix_hist<false, SORT_IPT>(D, plan, s, kin, shift, hist, disorder);
+            launch_counts<false, SORT_IPT>(pass, counting, D, plan, s, kin, hist, disorder, range);
             launch_scan(hist, hoff, scanp, len, (len + SCAN_TILE - 1) / SCAN_TILE, s, disorder);
             launch_radix_scatter<false, SORT_IPT>(D, plan, s, kin, vin, kout, vout, shift, hoff,
                                                   disorder);

@@ -171,3 +171,30 @@ def test_light_lookup_with_and_without_the_cache(rt, n, S, mode):
     if mode == "nearest":
         keep = bucket_edge_mask(uv.numpy(), tbn.numpy(), np.ones((N, 3), np.float32), W, H, n)
     check_fwd(host(out), ref, keep)
+
+
+# The order check counts the first pass's digits up to 2^23 records; planned
+# fragments (checked against the plain ones bit for bit) skip the sort on either
+# side.
+@pytest.mark.parametrize("N", [1 << 23, (1 << 23) + 1])
+def test_order_checks_that_count_and_not(rt, N):
+    W, H, n = 64, 64, 4
+    g = torch.Generator(device=DEV).manual_seed(5)
+    uv = torch.rand((N, 2), generator=g, device=DEV)
+    view = torch.randn((N, 3), generator=g, device=DEV)
+    view[:, 2] = view[:, 2].abs() + 0.5
+    tbn = torch.eye(3, device=DEV).expand(N, 3, 3).contiguous()
+    go = torch.randn((N, 1), generator=g, device=DEV)
+    tex = rt.Texture(torch.zeros((H, W, n, n, 1), device=DEV), W, H, n, 1)
+    want = dict(want_view=False, want_uv=False)
+    gt, _, _ = rt.lookup_bwd(tex, uv, tbn, view, go, **want)
+    order, *p = rt.plan_fragments(tex, uv, tbn, view)
+    o = order.long()
+    pt, _, _ = rt.lookup_bwd(tex, *p, go[o].contiguous(), **want)
+    assert torch.equal(pt, gt)
+    assert torch.equal(torch.bincount(o, minlength=N), torch.ones(N, dtype=torch.int64, device=DEV))
+    # each fragment's tap weights sum to one: the gradient carries the mass of go,
+    # within the rounding of the sums (2^-24 of the summed magnitudes, a factor of
+    # 16 for the depth of the sums)
+    err = float((gt.double().sum() - go.double().sum()).abs())
+    assert err <= 16 * 2.0 ** -24 * float(go.double().abs().sum())
