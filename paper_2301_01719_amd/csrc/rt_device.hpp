@@ -243,9 +243,16 @@ struct RowBits {
 // waited for.  Two texels of a row by one access halve the instructions of a
 // gather, which is bound by the lines that each of them touches (64 when every
 // lane reads another bucket).  Four buckets, 8.4M fragments of an FP8 RGBA
-// texture: lookup 511 -> 284 us, fragment pass of the backward 509 -> 418 (390 with the rest of it shortened);
-// 2.1M fragments of a BF16 RGBA one: lookup 205 -> 155.  One bucket: the same
-// to 5% less.
+// texture: lookup 511 -> 285 us, fragment pass of the backward 509 -> 418 (387
+// with the rest of it shortened); 2.1M fragments of a BF16 RGBA one: lookup 205 ->
+// 155.  One bucket: the same to 5% less.
+//
+// The order of the loads is fixed, bucket by bucket (the barriers): one such load
+// brings as many lines as a quarter of the L1 holds, and the accesses to a bucket's
+// lines have to follow each other while they are there.  Left to the scheduler,
+// 2.5M random rays on a 64 x 32 matrix of 8 x 8, four buckets: FP8 RGBA 97 us and
+// 68 so, BF16 RGBA 91 and 71, FP32 88 and 59, FP32 RGBA 135 and 98 (a texel a load,
+// waited for by bucket: 133, 119, 66, 104).
 template <int FMT, int C, int NB>
 __device__ __forceinline__ void load_rows(const unsigned char* const src[NB], int n,
                                           RowBits<FMT, C> row[NB][2]) {
@@ -257,12 +264,14 @@ __device__ __forceinline__ void load_rows(const unsigned char* const src[NB], in
         for (int k = 0; k < NB; k++) {
             row[k][0].load_each(src[k], src[k] + second);
             row[k][1].load_each(src[k] + below, src[k] + below + second);
+            __builtin_amdgcn_sched_barrier(0);
         }
     } else if (n >= 2) {  // the second column is x0 + 1 (see footprint)
 #pragma unroll
         for (int k = 0; k < NB; k++) {
             row[k][0].load_two(src[k]);
             row[k][1].load_two(src[k] + below);
+            __builtin_amdgcn_sched_barrier(0);
         }
     } else {
 #pragma unroll
