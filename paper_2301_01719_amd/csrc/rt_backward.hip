@@ -1812,9 +1812,13 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
     p->off_keys1 = take((size_t)R * 4);
     p->off_vals0 = take((size_t)R * 4);
     p->off_vals1 = take((size_t)R * 4);
-    p->off_hist = take((size_t)p->scan_len * 4);
-    p->off_hoff = take((size_t)p->scan_len * 4);
-    p->off_scanp = take((size_t)(p->scan_blocks + 1) * 4);
+    // A small sort needs the counts only.  Fewer keys per thread make more counts
+    // (up to SMALL_SORT_COUNTS / 2), so larger sorts reserve as many: a workspace
+    // of some size serves fewer fragments too.
+    const int64_t least = std::min<int64_t>(SMALL_SORT_COUNTS / 2, (int64_t)p->bins * tiles_of(4));
+    p->off_hist = take((size_t)std::max(p->scan_len, least) * 4);
+    p->off_hoff = take(p->small_sort ? 0 : (size_t)p->scan_len * 4);
+    p->off_scanp = take(p->small_sort ? 0 : (size_t)(p->scan_blocks + 1) * 4);
     // the disorder word, and right after it (both are cleared in one go) the
     // big-bucket counters and the bucket ranges
     p->off_disorder = take(256);

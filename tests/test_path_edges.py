@@ -198,3 +198,16 @@ def test_order_checks_that_count_and_not(rt, N):
     # 16 for the depth of the sums)
     err = float((gt.double().sum() - go.double().sum()).abs())
     assert err <= 16 * 2.0 ** -24 * float(go.double().abs().sum())
+
+
+# A workspace sized for more fragments serves fewer (up to 4M records, where the
+# digits change), also where a smaller sort takes smaller tiles.
+@pytest.mark.parametrize("W,H,n", [(16, 16, 16), (64, 32, 13), (3, 5, 1), (512, 512, 16)])
+@pytest.mark.parametrize("mode", ["nearest", "bilinear"])
+def test_workspaces_grow_with_the_fragments(rt, W, H, n, mode):
+    tex = rt.Texture(torch.empty((H, W, n, n, 1), device=DEV), W, H, n, 1)
+    counts = sorted({max(1, (k << s) + d) for s in range(6, 20) for k in (1, 3) for d in (-1, 0, 1)
+                     if (k << s) < (1 << 20)})
+    for size in (rt.bwd_workspace_bytes, rt.plan_workspace_bytes):
+        sizes = [size(tex, c, mode) for c in counts]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:]))
