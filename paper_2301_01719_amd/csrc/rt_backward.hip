@@ -14,7 +14,7 @@
 //                       keep record order, so the sorted sequence depends only
 //                       on the inputs.
 //   3. k_bucket_ranges  [start, end) of every bucket in the sorted records.
-//      k_payload        (buckets of at most 8 records on average, in its
+//      k_payload        (buckets of few records on average, in its
 //                       place) the same, and the fractions and weighted
 //                       upstream gradient of the records of buckets with at
 //                       most 64 records, written in sorted order.
@@ -2114,13 +2114,16 @@ hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, cons
     if (R > 0) dis = launch_sort_records(plan, ws, range, s, &skeys, &svals);
 
     // 3. ranges of the sorted records, with the records' payload in sorted
-    // order when buckets hold 8 records or fewer on average: a window of 64
-    // records then serves several buckets, of which each would gather again;
-    // both return at once when the sort did.  Payload, windows and big pass
-    // against ranges, windows and big pass, us: 2 records a bucket 756 and 788;
-    // 12: 317 and 299; 20: 70 and 63; 23 (random rays): 96 and 99; 48: 140 and
-    // 135; 64 (RGB): 133 and 95; 32 with bilinear buckets: 397 and 353.
-    const bool pay = R > 0 && R <= 8 * nb;
+    // order when buckets hold few records on average: a window of 64 records then
+    // serves several buckets, of which each would gather again.  Few is 8 up to
+    // 2^23 records, whose fragments the last-level cache holds, and 24 beyond,
+    // where the payload's own kernel has more gathers in flight.  Both return at
+    // once when the sort did.  Payload, windows and big pass against ranges,
+    // windows and big pass, us: 2M records, 2 a bucket 756 and 788; 4.1M, 12: 317
+    // and 299; 1.3M, 20: 70 and 63; 8.3M, 32: 436 and 381; 4.2M, 64 (RGB): 133 and
+    // 95; 16.6M, 16: 1180 and 1239; 33M, 32: 1649 and 1594; 66M, 16: 4610 and
+    // 5211, 64: 2846 and 2325; 33M with bilinear buckets, 32: 1609 and 1596.
+    const bool pay = R > 0 && R <= (R <= (int64_t(1) << 23) ? 8 : 24) * nb;
     if (R > 0 && !pay) {
         prof_begin(K_BUCKET_RANGES, s);
         hipLaunchKernelGGL(k_bucket_ranges, dim3((uint32_t)((R + 1023) / 1024)), dim3(256), 0, s,

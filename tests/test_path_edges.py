@@ -83,7 +83,7 @@ def test_sorts_of_either_side_of_their_limits(rt, W, H, n, C, N, mode):
     _check_backward(rt, *f, W, H, n, C, mode, N)
 
 
-# A payload is written up to 8 records a bucket on average.
+# A payload is written up to 8 records a bucket on average (sorts of this size).
 @pytest.mark.parametrize("C", [1, 2, 3, 4])
 @pytest.mark.parametrize("N,mode", [(8 * 2048, "nearest"), (8 * 2048 + 1, "nearest"),
                                     (2 * 2048, "bilinear"), (2 * 2048 + 1, "bilinear")])
