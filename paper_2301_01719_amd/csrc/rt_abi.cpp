@@ -457,9 +457,9 @@ size_t rt_plan_workspace(const rt_texture* t, int64_t count, uint32_t flags) {
     try {
         if (!t || count < 0 || flags > RT_BUCKET_BILINEAR) return 0;
         rt::BwdPlan p;
-        if (!rt::plan_backward(t->view.W, t->view.H, t->view.n, 1, count, rt::MODE_NEAREST, &p))
+        if (!rt::plan_visit(t->view.W, t->view.H, t->view.n, count, &p))
             return 0;
-        return p.sort_total;
+        return p.total;
     } catch (...) {
         return 0;
     }
@@ -482,7 +482,7 @@ rt_status rt_plan_fragments(const rt_texture* t, const rt_fragments* f, uint32_t
     if (st != RT_OK) return st;
     if (flags > RT_BUCKET_BILINEAR) return fail(RT_ERR_INVALID_ARG, "unknown flags 0x%x", flags);
     rt::BwdPlan plan;
-    if (!rt::plan_backward(t->view.W, t->view.H, t->view.n, 1, f->count, rt::MODE_NEAREST, &plan))
+    if (!rt::plan_visit(t->view.W, t->view.H, t->view.n, f->count, &plan))
         return fail(RT_ERR_UNSUPPORTED, "sort key (W*H*n*n) beyond 32 bits");
     const int64_t N = f->count;
     if (N == 0) return ok();
@@ -505,9 +505,9 @@ rt_status rt_plan_fragments(const rt_texture* t, const rt_fragments* f, uint32_t
     }
     if (!ws) return fail(RT_ERR_INVALID_ARG, "workspace is NULL");
     if (!aligned(ws, 256)) return fail(RT_ERR_INVALID_ARG, "workspace must be 256-byte aligned");
-    if (ws_bytes < plan.sort_total)
+    if (ws_bytes < plan.total)
         return fail(RT_ERR_WORKSPACE_TOO_SMALL, "workspace has %zu bytes, %zu needed", ws_bytes,
-                    plan.sort_total);
+                    plan.total);
     hipError_t e = rt::launch_plan(t->view, (int)flags, f->uv, f->tbn, f->view, fragmap(f), plan,
                                    ws, order, uv_out, tbn_out, view_out, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "plan launch");

@@ -1748,6 +1748,30 @@ static int ceil_log2(uint64_t x) {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// Radix tiles of R records with ipt keys per thread.
+static int64_t radix_tiles(int64_t R, int ipt) {
+    return (R + SORT_THREADS * ipt - 1) / (SORT_THREADS * ipt);
+}
+
+// The digit counts of the sort, their scanned offsets and the scan's sums, from
+// offset o of the workspace on; returns where they end.  A small sort needs the
+// counts only.  Fewer keys per thread make more counts (up to
+// SMALL_SORT_COUNTS / 2), so larger sorts reserve as many: the tables of fewer
+// records fit as well.
+static size_t place_tables(BwdPlan* p, size_t o) {
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o += align256(bytes);
+        return at;
+    };
+    const int64_t least = std::min<int64_t>(SMALL_SORT_COUNTS / 2,
+                                            (int64_t)p->bins * radix_tiles(p->records, 4));
+    p->off_hist = take((size_t)std::max(p->scan_len, least) * 4);
+    p->off_hoff = take(p->small_sort ? 0 : (size_t)p->scan_len * 4);
+    p->off_scanp = take(p->small_sort ? 0 : (size_t)(p->scan_blocks + 1) * 4);
+    return o;
+}
+
 bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, bool sparse) {
     // the accumulation holds four bucket tiles per workgroup in LDS (64 KiB)
     if ((int64_t)n * n * C > 4096) return false;
@@ -1785,17 +1809,16 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
     // tiles, 2^8 digits), 600,000 the same either way (147 tiles, 2^8 digits),
     // 1,000,000 343 and 398 us (245 tiles, 2^10 digits).
     p->bins = 1 << std::max(8, widest);
-    const auto tiles_of = [&](int ipt) { return (R + SORT_THREADS * ipt - 1) / (SORT_THREADS * ipt); };
     p->sort_ipt = SORT_IPT;
-    p->small_sort = tiles_of(SORT_IPT) * p->bins <= SMALL_SORT_COUNTS;
+    p->small_sort = radix_tiles(R, SORT_IPT) * p->bins <= SMALL_SORT_COUNTS;
     // Its few tiles leave most of the chip idle, and the rounds of a tile run one
     // after the other: fewer keys per thread while the table stays below half
     // that size (65,536 records and 2^9 digits: 46.8 us with 16, 44.7 with 8, 40.1
     // with 4 keys; 50,001 and 2^10, past it: 45.7 with 8, 50.0 with 4).
     while (p->small_sort && p->sort_ipt > 4 &&
-           tiles_of(p->sort_ipt / 2) * p->bins <= SMALL_SORT_COUNTS / 2)
+           radix_tiles(R, p->sort_ipt / 2) * p->bins <= SMALL_SORT_COUNTS / 2)
         p->sort_ipt /= 2;
-    p->tiles = tiles_of(p->sort_ipt);
+    p->tiles = radix_tiles(R, p->sort_ipt);
     p->scan_len = (int64_t)p->bins * p->tiles;
     p->scan_blocks = (p->scan_len + SCAN_TILE - 1) / SCAN_TILE;
     p->chunks = (R + PIECE - 1) / PIECE;
@@ -1806,26 +1829,19 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
         o += align256(bytes);
         return at;
     };
-    // the sort's buffers and the disorder word first: a visit plan's
-    // workspace is this prefix
     p->off_keys0 = take((size_t)R * 4);
     p->off_keys1 = take((size_t)R * 4);
     p->off_vals0 = take((size_t)R * 4);
     p->off_vals1 = take((size_t)R * 4);
-    // A small sort needs the counts only.  Fewer keys per thread make more counts
-    // (up to SMALL_SORT_COUNTS / 2), so larger sorts reserve as many: a workspace
-    // of some size serves fewer fragments too.
-    const int64_t least = std::min<int64_t>(SMALL_SORT_COUNTS / 2, (int64_t)p->bins * tiles_of(4));
-    p->off_hist = take((size_t)std::max(p->scan_len, least) * 4);
-    p->off_hoff = take(p->small_sort ? 0 : (size_t)p->scan_len * 4);
-    p->off_scanp = take(p->small_sort ? 0 : (size_t)(p->scan_blocks + 1) * 4);
     // the disorder word, and right after it (both are cleared in one go) the
     // big-bucket counters and the bucket ranges
     p->off_disorder = take(256);
-    p->sort_total = o;
     p->off_range = take((size_t)BIG_LISTS * BIG_STRIDE * 4 + (size_t)nb * 8);
     p->clear_bytes = o - p->off_disorder;
     p->off_wrec = take((size_t)N * (mode == MODE_NEAREST ? 8 : 16));
+    // The sort's tables share the memory of what is written after the sort (12
+    // bytes a record and more: the tables add nothing from 2049 records on).
+    const size_t tables_end = place_tables(p, o);
     p->off_payf = take((size_t)R * 8);
     p->off_payg = take((size_t)R * 4 * C);
     // big-bucket lists: list l receives the runs r of BIG_RUN groups with
@@ -1838,7 +1854,13 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
     p->big_cap = std::max<int64_t>(1, std::min<int64_t>(per_list, R / 65));
     p->off_biglist = take((size_t)BIG_LISTS * p->big_cap * 4);
     p->off_part = take((size_t)p->chunks * 2 * p->tile_elems * 4);
-    p->total = o;
+    p->total = std::max(o, tables_end);
+    return true;
+}
+
+bool plan_visit(int W, int H, int n, int64_t N, BwdPlan* p) {
+    if (!plan_backward(W, H, n, 1, N, MODE_NEAREST, p)) return false;
+    p->total = place_tables(p, p->off_range);
     return true;
 }
 

@@ -132,11 +132,10 @@ struct BwdPlan {
     int64_t buckets;      // W * H
     uint32_t sentinel;    // sparse plans: the key of a fragment whose upstream
                           // gradient is zero (past every bucket); 0 otherwise
-    // workspace offsets (bytes); the sort's buffers and the disorder word
-    // come first and end at sort_total
-    size_t off_keys0, off_keys1, off_vals0, off_vals1, off_hist, off_hoff, off_scanp,
-        off_disorder, sort_total, off_range, off_wrec, off_payf, off_payg, off_biglist,
-        off_part, total;
+    // workspace offsets (bytes); hist, hoff and scanp (read by the sort only)
+    // share their bytes with payf and what follows it
+    size_t off_keys0, off_keys1, off_vals0, off_vals1, off_disorder, off_range, off_wrec,
+        off_hist, off_hoff, off_scanp, off_payf, off_payg, off_biglist, off_part, total;
     size_t clear_bytes;   // cleared before the order check: the disorder word, the
                           // big-bucket counters, the ranges (from off_disorder on)
 };
@@ -152,6 +151,9 @@ constexpr int BIG_RUN = 64;     // consecutive groups that append to one list
 // keys sort past every bucket and are skipped), at the price of one key bit.
 bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p,
                    bool sparse = false);
+// A visit plan's sort of N records: of the workspace it has the keys, the
+// values, the disorder word and, right after it, the sort's tables.
+bool plan_visit(int W, int H, int n, int64_t N, BwdPlan* p);
 
 // Where the accumulation writes the tile of bucket b: the buckets of one
 // gradient, or those of the levels of a chain numbered one level after the
@@ -218,8 +220,8 @@ hipError_t launch_vq_update(const float* x, const int32_t* assign, float* codebo
 // Visit plan: the fragments ordered by their nearest-mode record key (or the
 // key of their first bucket in the bilinear-bucket mode), stable in the
 // fragment index; writes order[k] (the caller's index of planned fragment k)
-// and the planned G-buffer.  plan: plan_backward(W, H, n, 1, N, MODE_NEAREST);
-// the workspace needs plan.sort_total bytes.
+// and the planned G-buffer.  plan: plan_visit(W, H, n, N); the workspace needs
+// plan.total bytes.
 hipError_t launch_plan(const TexView& t, int mode, const float* uv, const float* tbn,
                        const float* view, const FragMap& m, const BwdPlan& plan, void* ws,
                        int32_t* order, float* uv_out, float* tbn_out, float* view_out,
