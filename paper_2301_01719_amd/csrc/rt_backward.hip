@@ -1753,11 +1753,23 @@ static int64_t radix_tiles(int64_t R, int ipt) {
     return (R + SORT_THREADS * ipt - 1) / (SORT_THREADS * ipt);
 }
 
+// Digits of at most 10 bits up to this many records, 9 beyond, where the
+// histograms, their scan and the scatter's LDS, which grow as 2^D, cost more than
+// a pass saves.
+constexpr int64_t WIDE_DIGIT_RECORDS = int64_t(1) << 22;
+
+// log2 of the counts of a tile: the bits spread evenly over as few passes as
+// digits of `most` bits allow, in a kernel of at least 8.
+static int tile_bits(int key_bits, int most) {
+    const int passes = (key_bits + most - 1) / most;
+    return std::max(8, (key_bits + passes - 1) / passes);
+}
+
 // The digit counts of the sort, their scanned offsets and the scan's sums, from
 // offset o of the workspace on; returns where they end.  A small sort needs the
-// counts only.  Fewer keys per thread make more counts (up to
-// SMALL_SORT_COUNTS / 2), so larger sorts reserve as many: the tables of fewer
-// records fit as well.
+// counts only.  A workspace of some size serves fewer records as well, so a sort
+// reserves as many counts as any of fewer records has: fewer keys per thread make
+// more of them (up to SMALL_SORT_COUNTS / 2), and so do wider digits.
 static size_t place_tables(BwdPlan* p, size_t o) {
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -1766,9 +1778,13 @@ static size_t place_tables(BwdPlan* p, size_t o) {
     };
     const int64_t least = std::min<int64_t>(SMALL_SORT_COUNTS / 2,
                                             (int64_t)p->bins * radix_tiles(p->records, 4));
-    p->off_hist = take((size_t)std::max(p->scan_len, least) * 4);
-    p->off_hoff = take(p->small_sort ? 0 : (size_t)p->scan_len * 4);
-    p->off_scanp = take(p->small_sort ? 0 : (size_t)(p->scan_blocks + 1) * 4);
+    int64_t counts = std::max(p->scan_len, least);
+    if (p->records > WIDE_DIGIT_RECORDS)
+        counts = std::max(counts, radix_tiles(WIDE_DIGIT_RECORDS, SORT_IPT)
+                                      << tile_bits(std::max(1, p->key_bits), 10));
+    p->off_hist = take((size_t)counts * 4);
+    p->off_hoff = take(p->small_sort ? 0 : (size_t)counts * 4);
+    p->off_scanp = take(p->small_sort ? 0 : (size_t)((counts + SCAN_TILE - 1) / SCAN_TILE + 1) * 4);
     return o;
 }
 
@@ -1788,19 +1804,15 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
     p->buckets = nb;
     p->sentinel = !sparse ? 0u
                   : (p->key_bits >= 32 ? 0xFFFFFFFFu : (uint32_t)((1ull << p->key_bits) - 1));
-    // as few passes as digits of at most 10 bits allow (9 bits beyond 4M
-    // records, where the histograms, their scan and the scatter's LDS, which
-    // grow as 2^D, cost more than a pass saves), the bits spread evenly
     const int kb = std::max(1, p->key_bits);
-    const int maxd = R <= (1ll << 22) ? 10 : 9;
+    const int maxd = R <= WIDE_DIGIT_RECORDS ? 10 : 9;
     p->passes = (kb + maxd - 1) / maxd;
-    int at = 0, widest = 0;
+    int at = 0;
     for (int q = 0; q < 4; q++) {
         const int bits = q < p->passes ? kb / p->passes + (q < kb % p->passes ? 1 : 0) : 0;
         p->digit_bits[q] = bits;
         p->digit_shift[q] = at;
         at += bits;
-        widest = std::max(widest, bits);
     }
     // A small sort is bound by its launches, so it makes fewer (its scatters add
     // the tiles' digit counts up themselves, see launch_sort_records), at the
@@ -1808,7 +1820,7 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
     // backward of 200,000 records took 104 us with the scans and 77 without (49
     // tiles, 2^8 digits), 600,000 the same either way (147 tiles, 2^8 digits),
     // 1,000,000 343 and 398 us (245 tiles, 2^10 digits).
-    p->bins = 1 << std::max(8, widest);
+    p->bins = 1 << tile_bits(kb, maxd);
     p->sort_ipt = SORT_IPT;
     p->small_sort = radix_tiles(R, SORT_IPT) * p->bins <= SMALL_SORT_COUNTS;
     // Its few tiles leave most of the chip idle, and the rounds of a tile run one

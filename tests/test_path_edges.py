@@ -211,3 +211,16 @@ def test_workspaces_grow_with_the_fragments(rt, W, H, n, mode):
     for size in (rt.bwd_workspace_bytes, rt.plan_workspace_bytes):
         sizes = [size(tex, c, mode) for c in counts]
         assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+# The same where the digits change, at 2^22 records (nearest: fragments; bilinear
+# buckets: four a fragment; a visit plan: one a fragment in either mode).
+@pytest.mark.parametrize("W,H,n,C", [(64, 64, 16, 1), (512, 512, 16, 1), (65, 1117, 2, 3)])
+@pytest.mark.parametrize("mode", ["nearest", "bilinear"])
+def test_workspaces_grow_where_the_digits_change(rt, W, H, n, C, mode):
+    tex = rt.Texture(torch.empty((H, W, n, n, C), device=DEV), W, H, n, C)
+    counts = sorted({(k << s) // 16 + d for s in range(20, 24) for k in range(16, 33)
+                     for d in (-1, 0, 1)})
+    for size in (rt.bwd_workspace_bytes, rt.plan_workspace_bytes):
+        sizes = [size(tex, c, mode) for c in counts]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:]))
