@@ -15,6 +15,7 @@ import torch
 
 import oracle
 from helpers import away_from_edges, bucket_edge_mask, check_fwd, check_grad_tex, host
+from test_plan import _keys
 from test_shadow import _bit_texture, _frags, _light_vecs
 
 pytestmark = pytest.mark.gpu
@@ -224,3 +225,36 @@ def test_workspaces_grow_where_the_digits_change(rt, W, H, n, C, mode):
     for size in (rt.bwd_workspace_bytes, rt.plan_workspace_bytes):
         sizes = [size(tex, c, mode) for c in counts]
         assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+# One pair of fragments swapped across a bucket boundary of a planned G-buffer:
+# the order check that counts digits (up to 2^23 records) and the one that does
+# not find it inside a group of 1024 keys, between two groups and in the partial
+# last one.  The other groups' keys are in order, so they write the ranges of
+# buckets that the sort then moves: the gradient is the plain one's, bit for bit,
+# only if the check finds the descent and every such range is written again.
+@pytest.mark.parametrize("N", [(1 << 22) + 1524, (1 << 23) + 1524])
+@pytest.mark.parametrize("where", ["first", "inside", "between", "last"])
+def test_one_descent_is_found_by_either_order_check(rt, N, where):
+    W, H, n = 1024, 1024, 4
+    g = torch.Generator(device=DEV).manual_seed(6)
+    uv = torch.rand((N, 2), generator=g, device=DEV)
+    view = torch.randn((N, 3), generator=g, device=DEV)
+    view[:, 2] = view[:, 2].abs() + 0.5
+    tbn = torch.eye(3, device=DEV).expand(N, 3, 3).contiguous()
+    go = torch.randn((N, 1), generator=g, device=DEV)
+    tex = rt.Texture(torch.zeros((H, W, n, n, 1), device=DEV), W, H, n, 1)
+    want = dict(want_view=False, want_uv=False)
+    gt, _, _ = rt.lookup_bwd(tex, uv, tbn, view, go, **want)
+    order, *p = rt.plan_fragments(tex, uv, tbn, view)
+    bucket = _keys(rt, tex, *p, W, n, "nearest") // (n * n)
+    steps = np.nonzero(np.diff(bucket) > 0)[0]  # a and a + 1 lie in different buckets
+    at = {"first": steps, "inside": steps[(steps > N // 2) & (steps % 1024 == 500)],
+          "between": steps[(steps > N // 3) & (steps % 1024 == 1023)],
+          "last": steps[steps >= N // 1024 * 1024]}[where]
+    a = int(at[0])
+    perm = torch.arange(N, device=DEV)
+    perm[a], perm[a + 1] = a + 1, a
+    o = order.long()[perm]
+    sgt, _, _ = rt.lookup_bwd(tex, *(x[perm].contiguous() for x in p), go[o].contiguous(), **want)
+    assert torch.equal(sgt, gt)
