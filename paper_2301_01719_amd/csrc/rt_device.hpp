@@ -186,6 +186,21 @@ struct RowBits {
     }
     // exactly the two texels' bytes
     __device__ __forceinline__ void load_two(const unsigned char* src) { take<2 * TEXEL>(src); }
+    // the same for texels of three 2-byte values, by a 4-byte aligned access of 12
+    // bytes (from the value before src where src lies between words) and one of
+    // the last value
+    __device__ __forceinline__ void load_two_aligned(const unsigned char* src) {
+        static_assert(TEXEL == 6, "12 bytes, 2-byte aligned");
+        struct __attribute__((packed, aligned(4))) Words {
+            uint32_t x, y, z;
+        };
+        const uint32_t odd = (uint32_t)(uintptr_t)src & 2u;
+        const Words p = *(const Words*)(src - odd);
+        const uint32_t last = *(const uint16_t*)(src + 10);
+        w[0] = __builtin_amdgcn_alignbit(p.y, p.x, 8 * odd);
+        w[1] = __builtin_amdgcn_alignbit(p.z, p.y, 8 * odd);
+        w[2] = __builtin_amdgcn_alignbit(last, p.z, 8 * odd);
+    }
     // the texels at a and b
     __device__ __forceinline__ void load_each(const unsigned char* a, const unsigned char* b) {
         static_assert(TEXEL % 4 == 0, "whole words");
@@ -253,7 +268,15 @@ struct RowBits {
 // 2.5M random rays on a 64 x 32 matrix of 8 x 8, four buckets: FP8 RGBA 97 us and
 // 68 so, BF16 RGBA 91 and 71, FP32 88 and 59, FP32 RGBA 135 and 98 (a texel a load,
 // waited for by bucket: 133, 119, 66, 104).
-template <int FMT, int C, int NB>
+//
+// ALIGNED (texels of three 2-byte values): by word-aligned accesses, for lookups
+// that come back to a bucket, as a light of several samples does: accesses of 12
+// bytes off the word boundaries lose what the L1 holds of it.  BF16 RGB, a light
+// of 16 samples, one bucket, 2M fragments on a 512 x 512 matrix of 16 x 16, a texel
+// an access, two by one, two aligned: random rays 920, 1360 and 911 us, image
+// order 257, 109 and 107; on a 64 x 32 matrix of 8 x 8 546, 362 and 316.  With four
+// buckets in image order the aligned form is the slower one (687, 270 and 305).
+template <int FMT, int C, int NB, bool ALIGNED = false>
 __device__ __forceinline__ void load_rows(const unsigned char* const src[NB], int n,
                                           RowBits<FMT, C> row[NB][2]) {
     using Row = RowBits<FMT, C>;
@@ -269,8 +292,13 @@ __device__ __forceinline__ void load_rows(const unsigned char* const src[NB], in
     } else if (n >= 2) {  // the second column is x0 + 1 (see footprint)
 #pragma unroll
         for (int k = 0; k < NB; k++) {
-            row[k][0].load_two(src[k]);
-            row[k][1].load_two(src[k] + below);
+            if constexpr (ALIGNED) {
+                row[k][0].load_two_aligned(src[k]);
+                row[k][1].load_two_aligned(src[k] + below);
+            } else {
+                row[k][0].load_two(src[k]);
+                row[k][1].load_two(src[k] + below);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     } else {

@@ -43,8 +43,8 @@ __device__ __forceinline__ void blend_staged(const void* bucket, int n, const Fo
 
 // The taps of NB buckets bk around footprint p, blended bucket by bucket and
 // added to acc with weights wgt.  DICT: a bucket is read through the dictionary
-// (its entry in the codebook, times its gain).
-template <int FMT, int C, int NB, bool DICT = false>
+// (its entry in the codebook, times its gain).  ALIGNED: see load_rows.
+template <int FMT, int C, int NB, bool DICT = false, bool ALIGNED = false>
 __device__ __forceinline__ void buckets_bilerp(const TexView& t, const int64_t bk[NB],
                                                const Foot& p, const float wgt[NB], float acc[4]) {
     const int n = t.n;
@@ -81,7 +81,7 @@ __device__ __forceinline__ void buckets_bilerp(const TexView& t, const int64_t b
             src[k] = (const unsigned char*)t.data +
                      (b[k] * (int64_t)(n * n) + p.y0 * n + p.x0) * Row::TEXEL;
         Row row[NB][2];
-        load_rows<FMT, C, NB>(src, n, row);
+        load_rows<FMT, C, NB, ALIGNED>(src, n, row);
 #pragma unroll
         for (int k = 0; k < NB; k++) f[k] *= bucket_factor<FMT>(t.scales, b[k]);
 #pragma unroll
@@ -561,7 +561,8 @@ __global__ __launch_bounds__(256) void k_lookup_light(TexView t, const float* __
                 }
             }
         } else {
-            buckets_bilerp<FMT, C, NB, DICT>(t, bk, footprint(sx, sy, n), bw, acc);
+            constexpr bool ALIGNED = FMT == FMT_BF16 && C == 3 && NB == 1 && !DICT;
+            buckets_bilerp<FMT, C, NB, DICT, ALIGNED>(t, bk, footprint(sx, sy, n), bw, acc);
         }
     }
 #pragma unroll

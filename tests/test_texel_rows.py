@@ -57,3 +57,41 @@ def test_rows_of_two_texels(fmt, C, n, mode):
     rnd, _ = oracle.lookup_bwd_round(otex, *h, go.numpy(), round_s(n), round_w(W, H, h[0]), mode=m)
     check_grad_vec(host(gv)[keep], ref["grad_view"][keep], ref["scale_view"][keep],
                    go.numpy()[keep], rnd[keep])
+
+
+# Lights read the rows of a plain texture as the lookups do, those of BF16 RGB with
+# one bucket by word-aligned accesses: rows that start on a word and between two,
+# the first and the last texels of the allocation among them.
+@pytest.mark.parametrize("mode", ["nearest", "bilinear"])
+@pytest.mark.parametrize("n", [1, 2, 3, 5])
+@pytest.mark.parametrize("C", [1, 2, 3, 4])
+@pytest.mark.parametrize("fmt", ["f32", "bf16", "fp8"])
+def test_rows_of_two_texels_under_lights(fmt, C, n, mode):
+    from paper_2301_01719_amd import radtex as rt
+    from test_shadow import _frags, _light_vecs
+    W, H, N, S = 3, 1, 600, 5
+    g = torch.Generator().manual_seed(1000 * n + 10 * C + len(fmt))
+    values = torch.rand((H, W, n, n, C), generator=g)
+    tex = rt.Texture(values.to(DEV), W, H, n, C)
+    otex = oracle.Tex(values.numpy(), W, H, n, C)
+    if fmt != "f32":
+        codes, scales = rt.quantize(tex, fmt)
+        tex = rt.Texture(codes, W, H, n, C, fmt, scales)
+        ocodes, oscales = oracle.quantize(values.numpy(), W * H, n * n * C, FMT[fmt])
+        otex = oracle.Tex(ocodes, W, H, n, C, FMT[fmt], oscales)
+    uv, tbn, _ = _frags(n * 10 + C, N)
+    uv[0] = torch.tensor([0.5 / W, 0.5 / H])
+    uv[1] = torch.tensor([1 - 0.5 / W, 1 - 0.5 / H])
+    tbn[:2] = torch.eye(3)
+    vec = _light_vecs("directional", S, seed=n + C)
+    vec[0], vec[1] = torch.tensor([-1.0, -1.0, 0.0]), torch.tensor([1.0, 1.0, 0.0])
+    out = rt.lookup_light(tex, uv.to(DEV), tbn.to(DEV), rt.make_light(vec.numpy(), "directional"),
+                          mode=mode)
+    torch.cuda.synchronize()
+    m = oracle.MODE_NEAREST if mode == "nearest" else oracle.MODE_BILINEAR
+    ref = oracle.lookup_light(otex, uv.numpy(), tbn.numpy(), vec.numpy(),
+                              oracle.LIGHT_DIRECTIONAL, mode=m)
+    keep = None
+    if mode == "nearest":
+        keep = bucket_edge_mask(uv.numpy(), tbn.numpy(), torch.ones(N, 3).numpy(), W, H, n)
+    check_fwd(host(out), ref, keep)
