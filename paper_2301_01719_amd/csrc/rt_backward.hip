@@ -2160,14 +2160,21 @@ hipError_t launch_accumulate(int n, int C, int mode, const float* grad_out, cons
     // 3. ranges of the sorted records, with the records' payload in sorted
     // order when buckets hold few records on average: a window of 64 records then
     // serves several buckets, of which each would gather again.  Few is 8 up to
-    // 2^23 records, whose fragments the last-level cache holds, and 24 beyond,
-    // where the payload's own kernel has more gathers in flight.  Both return at
-    // once when the sort did.  Payload, windows and big pass against ranges,
-    // windows and big pass, us: 2M records, 2 a bucket 756 and 788; 4.1M, 12: 317
-    // and 299; 1.3M, 20: 70 and 63; 8.3M, 32: 436 and 381; 4.2M, 64 (RGB): 133 and
-    // 95; 16.6M, 16: 1180 and 1239; 33M, 32: 1649 and 1594; 66M, 16: 4610 and
-    // 5211, 64: 2846 and 2325; 33M with bilinear buckets, 32: 1609 and 1596.
-    const bool pay = R > 0 && R <= (R <= (int64_t(1) << 23) ? 8 : 24) * nb;
+    // 2^23 fragments, which the last-level cache holds, and 24 beyond, where the
+    // payload's own kernel has more gathers in flight.  Both return at once when the
+    // sort did.  Payload, windows and big pass against ranges, windows and big pass,
+    // us: 2M records, 2 a bucket 756 and 788; 4.1M, 12: 317 and 299; 1.3M, 20: 70 and
+    // 63; 8.3M, 32: 436 and 381; 4.2M, 64 (RGB): 133 and 95; 16.6M, 16: 1180 and
+    // 1239; 33M, 32: 1649 and 1594; 66M, 16: 4610 and 5211, 64: 2846 and 2325.
+    // Four buckets (four records a fragment; whole backwards of RGBA): 10.5M records
+    // of random rays, 8 a bucket 952 and 741, 16: 740 and 536; of four views in image
+    // order, 11: 803 and 735; 33M of random rays, 12: 2687 and 2236, of views, 11:
+    // 2685 and 2625, 14: 2368 and 2046; 33M of one view of a height field, 32: 1609
+    // and 1596.  Rays without any order lose where the gathers are short: 33M rays of
+    // one channel, 32 a bucket, 2776 and 3001 (four views of as many, 14: 2107 and
+    // 1826, so the line does not follow them).
+    const int64_t frags = mode == MODE_NEAREST ? R : R / 4;
+    const bool pay = R > 0 && R <= (frags <= (int64_t(1) << 23) ? 8 : 24) * nb;
     if (R > 0 && !pay) {
         prof_begin(K_BUCKET_RANGES, s);
         hipLaunchKernelGGL(k_bucket_ranges, dim3((uint32_t)((R + 1023) / 1024)), dim3(256), 0, s,

@@ -258,3 +258,34 @@ def test_one_descent_is_found_by_either_order_check(rt, N, where):
     o = order.long()[perm]
     sgt, _, _ = rt.lookup_bwd(tex, *(x[perm].contiguous() for x in p), go[o].contiguous(), **want)
     assert torch.equal(sgt, gt)
+
+
+# With bilinear buckets the line is at 8 records a bucket up to 2^23 fragments too,
+# also beyond 2^23 records: both sides of it, and one beyond 2^23 fragments, where
+# the payload is written up to 24.  Random rays, so nearly every window holds
+# several buckets.  The gradient is checked by blocks of fragments that a plain
+# backward of fewer records serves: it is linear, and sums of 8 parts in another
+# order stay within the rounding of the parts' sums (2^-24 of the summed magnitudes
+# an addition; at most 64 additions a texel and part here).
+@pytest.mark.parametrize("W,H,N", [(1280, 820, (1 << 21) + 1), (1280, 819, (1 << 21) + 1),
+                                   (1600, 1400, (1 << 23) + 1)])
+def test_payload_line_counts_fragments(rt, W, H, N):
+    n = 2
+    g = torch.Generator(device=DEV).manual_seed(9)
+    uv = torch.rand((N, 2), generator=g, device=DEV)
+    view = torch.randn((N, 3), generator=g, device=DEV)
+    view[:, 2] = view[:, 2].abs() + 0.5
+    tbn = torch.eye(3, device=DEV).expand(N, 3, 3).contiguous()
+    go = torch.randn((N, 1), generator=g, device=DEV)
+    tex = rt.Texture(torch.zeros((H, W, n, n, 1), device=DEV), W, H, n, 1)
+    want = dict(mode="bilinear", want_view=False, want_uv=False)
+    gt, _, _ = rt.lookup_bwd(tex, uv, tbn, view, go, **want)
+    total, mag = torch.zeros_like(gt, dtype=torch.float64), torch.zeros_like(gt, dtype=torch.float64)
+    for k in range(0, N, N // 8 + 1):
+        part = slice(k, k + N // 8 + 1)
+        f = [x[part].contiguous() for x in (uv, tbn, view)]
+        total += rt.lookup_bwd(tex, *f, go[part].contiguous(), **want)[0].double()
+        mag += rt.lookup_bwd(tex, *f, go[part].abs().contiguous(), **want)[0].double()
+    assert bool(((gt.double() - total).abs() <= 128 * 2.0 ** -24 * mag).all())
+    err = float((gt.double().sum() - go.double().sum()).abs())
+    assert err <= 16 * 2.0 ** -24 * float(go.double().abs().sum())
