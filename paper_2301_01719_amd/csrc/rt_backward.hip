@@ -1770,17 +1770,7 @@ static int tile_bits(int key_bits, int most) {
 // counts only.  A workspace of some size serves fewer records as well, so a sort
 // reserves as many counts as any of fewer records has: fewer keys per thread make
 // more of them (up to SMALL_SORT_COUNTS / 2), and so do wider digits.
-//
-// From TABLES_ALIGNED_FROM records on (where the payload's bytes hold the padding
-// too) the tables start on 64 KB: every workgroup of a small sort reads the whole
-// table of counts.  A backward of 1,048,576 records and 24 a bucket took 109.2 us
-// with the tables on 256 bytes or 4 KB, depending on the matrix, and 105.1 on 64
-// KB, 800,000 records 98.5 and 95.5.
-constexpr int64_t TABLES_ALIGNED_FROM = 16384;
-
 static size_t place_tables(BwdPlan* p, size_t o) {
-    constexpr size_t PAGE = 65536;
-    if (p->records >= TABLES_ALIGNED_FROM) o = (o + PAGE - 1) / PAGE * PAGE;
     auto take = [&](size_t bytes) {
         const size_t at = o;
         o += align256(bytes);
@@ -1862,8 +1852,14 @@ bool plan_backward(int W, int H, int n, int C, int64_t N, int mode, BwdPlan* p, 
     p->clear_bytes = o - p->off_disorder;
     p->off_wrec = take((size_t)N * (mode == MODE_NEAREST ? 8 : 16));
     // The sort's tables share the memory of what is written after the sort (12
-    // bytes a record and more: the tables add nothing from 2049 records on).
-    const size_t tables_end = place_tables(p, o);
+    // bytes a record and more: the tables add nothing from 2049 records on).  From
+    // 16,384 records on, where those bytes hold the padding too, they start on 64
+    // KB: every workgroup of a small sort reads the whole table of counts.  A
+    // backward of 1,048,576 records and 24 a bucket took 109.2 us with the tables on
+    // 256 bytes or 4 KB, depending on the matrix, and 105.1 on 64 KB, 800,000 records
+    // 98.5 and 95.5.
+    const size_t page = R >= 16384 ? 65536 : 256;
+    const size_t tables_end = place_tables(p, (o + page - 1) / page * page);
     p->off_payf = take((size_t)R * 8);
     p->off_payg = take((size_t)R * 4 * C);
     // big-bucket lists: list l receives the runs r of BIG_RUN groups with
