@@ -43,7 +43,6 @@ namespace rt {
 
 constexpr int SORT_THREADS = 256;
 constexpr int SORT_IPT = 16;  // keys per thread (4 or 8 in a small sort)
-constexpr int SORT_TILE = SORT_THREADS * SORT_IPT;  // 4096
 constexpr int SCAN_TILE = 4096;
 constexpr int64_t SCAN_FUSED_BLOCKS = 4096;
 
@@ -211,9 +210,10 @@ __device__ __forceinline__ void clear_words(const ClearWords& z) {
 // With one bucket a fragment: bound by its streams (92 to 104 bytes a
 // fragment, 5 TB/s).  With four: by the latency of the gathers at the wavefronts
 // that fit, so the registers are held to 128 (FP8 RGBA took 148, three
-// wavefronts a SIMD): 8.4M fragments, FP8 RGBA, 418 -> 404 us with 1139 vector
-// instructions instead of 1351, 390 with four wavefronts.  Keeping fewer
-// decoded taps (99 registers, 1315 instructions) gains no fifth.
+// wavefronts a SIMD): 8.4M fragments, FP8 RGBA, 418 us with three wavefronts, 387
+// with four and fewer instructions (982 vector instructions a wavefront, issued in
+// 71% of the cycles).  Keeping fewer decoded taps (99 registers, more
+// instructions) gains no fifth.
 template <int FMT, int C, int MODE>
 __global__ __launch_bounds__(256, 4) void k_bwd_fragment(
     TexView t, const float* __restrict__ uv, const float* __restrict__ tbn,
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256) void k_lod_bwd_fragment(
 }
 
 // ---------------------------------------------------------------------------
-// 2. stable LSD radix sort of (key, record index), 8-bit digits
+// 2. stable LSD radix sort of (key, record index), digits of up to 10 bits
 // ---------------------------------------------------------------------------
 
 // Records made in key order already (fragments visited in the order of a
@@ -1169,7 +1169,8 @@ __device__ __forceinline__ void accumulate_tails(int cell, const float v[4 * C],
 // third of the vector instructions and two thirds of the LDS ones.  The LDS
 // round trips of a block cost about as much as a step, so when a run reaches
 // more than LONG_RUN records (two blocks) the round scans whole runs instead
-// (64 views: 785 us with 8, 819 with 16; both keep the sums of a run in a tree).
+// (64 views in plan order 650 us with 8 and 660 with 16, 8 views with bilinear
+// buckets 525 and 530; both keep the sums of a run in a tree).
 constexpr int BLOCK = 4, LONG_RUN = 8;
 
 template <int C>
@@ -1544,9 +1545,10 @@ __global__ __launch_bounds__(256) void k_segacc(const uint32_t* __restrict__ ske
 // bucket.
 //
 // Bound by vector issue (87% of the cycles on the 64 views' 67M records, about
-// 265 vector instructions a round, 58% with bilinear buckets).  64 views: 973 us
+// 280 vector instructions a round; 58% on 8 views with bilinear buckets).  64 views: 973 us
 // when rounds scanned whole runs and carried the last one, 718 without the
-// carry, 655 since no round waits for a list entry, a range or an index.  8 views
+// carry, 650 since no round waits for a list entry, a range or an index (in image
+// order, where the records are gathered, 1255 us throughout).  8 views
 // with bilinear buckets (33.5M records, gathered): 600, 530, 520; 2867 buckets of
 // 70 records: 39 us, 10.5 (more lists).  Six wavefronts a SIMD instead of five
 // (80 registers, one spilled) give 638 us on the 64 views, but a launch that has
@@ -2287,8 +2289,8 @@ __global__ __launch_bounds__(256) void k_plan_keys(int W, int H, int n,
 // with one access a line instead of three, and stored by consecutive lanes,
 // past the caches, which keep the lines that later records gather from.  16.6M
 // records (two 4K views): 630 us with a lane per record, 498 with its stores
-// through LDS, 478 so (2.0 GB moved, 4.2 TB/s; the address unit was busy 85% of
-// the time before).
+// through LDS, 478 so (2.0 GB moved, 4.2 TB/s; the address unit is busy 85% of
+// the time).
 __global__ __launch_bounds__(256) void k_plan_gather(const uint32_t* __restrict__ svals,
                                                      int64_t N, const float* __restrict__ uv,
                                                      const float* __restrict__ tbn,

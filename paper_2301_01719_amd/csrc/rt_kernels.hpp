@@ -140,7 +140,7 @@ struct BwdPlan {
                           // big-bucket counters, the ranges (from off_disorder on)
 };
 constexpr int PIECE = 2048;  // records per chunk; buckets with more are "hot"
-constexpr int SEG_GROUP = 8;  // buckets per wavefront in the first accumulation pass
+constexpr int SEG_GROUP = 8;  // most buckets per wavefront in the first accumulation pass
 constexpr int BIG_LISTS = 64; // big-bucket lists, each with its own counter
 constexpr int BIG_STRIDE = 64;  // u32 between two counters (256 bytes)
 constexpr int HOT_FLAG = 1;     // u32 after counter 0: set when a bucket needs pass 2

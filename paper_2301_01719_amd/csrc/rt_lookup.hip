@@ -589,7 +589,11 @@ hipError_t launch_lookup_light(const TexView& t, int fmt, int mode, const float*
     prof_begin(K_LOOKUP_LIGHT, s);
     const uint32_t blocks = fragmap_blocks(m);
     if (fmt == FMT_BIT1) {
-        // the LDS copy of the buckets pays off once several samples read them
+        // the LDS copy of the buckets pays off once several samples read them (2M
+        // fragments on a 512 x 512 matrix of 16 x 16, us: 3 samples without it, 4
+        // with it: one bucket 20 and 23 in image order, 61 and 37 of random rays;
+        // four buckets 45 and 42, 226 and 71; 4 samples of four buckets gathered
+        // word by word 60 and 298)
         const bool cache = t.n <= 16 && lp.samples >= 4;
         if (mode == MODE_NEAREST) {
             if (cache) hipLaunchKernelGGL((k_lookup_light<FMT_BIT1, 1, MODE_NEAREST, true, false>), dim3(blocks), dim3(256), 0, s, t, uv, tbn, pos, lp, out, m);
